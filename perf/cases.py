@@ -114,10 +114,10 @@ def _nameless(*args, **kw):
 
 def _spec(case):
     """The grid spec of a case, the same dict as the benchmark's for its workloads."""
-    d0 = D0_MM if case["n_d0"] > 1 else 0.0
+    d0_lo, d0_hi = (-D0_MM, D0_MM) if case["n_d0"] > 1 else (0.0, 0.0)
     radii = WIDE_R_MM if case["kind"] == "count" else BARREL_R_MM
     s = dict(n_layers=len(radii), layer_r_mm=list(radii), b_tesla=B_TESLA, n_qpt=case["n_qpt"], qpt_lo=-1.0,
-             qpt_hi=1.0, n_phi=case["n_phi"], n_d0=case["n_d0"], d0_lo_mm=-d0, d0_hi_mm=d0,
+             qpt_hi=1.0, n_phi=case["n_phi"], n_d0=case["n_d0"], d0_lo_mm=d0_lo, d0_hi_mm=d0_hi,
              threshold=case["threshold"], n_z0=0, z0_lo_um=0, z0_hi_um=0, n_cot=0, cot_lo=0.0, cot_hi=0.0,
              rz_max_candidates=SERVE_CANDIDATES if case["kind"] == "serve" else 0)
     if case["rz"]:
