@@ -266,8 +266,8 @@ int hough_create(const hough_grid_spec *spec, const hough_limits *limits, int de
               dev_alloc(&c->d_scan_part, c->scan_blocks_max) && dev_alloc(&c->d_scan_off, c->scan_blocks_max + 1) &&
               dev_alloc(&c->d_dir_tab, size_t(E) * L * spec->n_phi) &&
               dev_alloc(&c->d_cl_rank, limits->max_peaks) &&
-              dev_alloc(&c->d_cl_part, cluster_blocks(limits->max_peaks)) &&
-              dev_alloc(&c->d_cl_part_off, cluster_blocks(limits->max_peaks) + 1) &&
+              dev_alloc(&c->d_cl_part, cluster_blocks_max(limits->max_peaks)) &&
+              dev_alloc(&c->d_cl_part_off, cluster_blocks_max(limits->max_peaks) + 1) &&
               dev_alloc(&c->d_rk_info, rk_info.size()) && dev_alloc(&c->d_rk_sorted, rk_sorted.size());
     if (!ok) {
         free_all(c);

@@ -220,6 +220,7 @@ hipError_t launch_scan_counts(hough_ctx *c, const uint32_t *counts, uint64_t n, 
 
 // Plateau clusters of a peak list (lock-free union-find, see k_cluster.hip).
 uint64_t cluster_blocks(uint64_t n);
+uint64_t cluster_blocks_max(uint64_t n);   // over the calls of up to n peaks
 hipError_t launch_clusters(hough_ctx *c, const hough_peak *peaks, uint64_t peak_capacity, const uint64_t *poff,
                            uint32_t n_events, uint32_t *labels, hough_cluster *clusters, uint64_t capacity,
                            uint64_t *coff, hipStream_t s);

@@ -327,3 +327,22 @@ def test_fit_rejects_d0_grid_and_reports_worst_difference(H):
     with pytest.raises(H.HoughError):
         ctx.cluster_fit(hits, pk, off, ctx.new_clusters(4), off, peak_capacity=16, capacity=4)
     print("largest fit differences from the oracle:", WORST)
+
+
+@pytest.mark.parametrize("n_d0,n_qpt,n_phi,density,seed", [
+    (1, 200, 64, 0.6, 20),        # two tiles of two-word rows
+    (1, 129, 64, 0.5, 21),        # a last tile of one row
+    (1, 37, 256, 0.65, 22),       # ragged last tile
+    (1, 7, 4096, 0.6, 23),        # two rows per tile, odd row count
+    (2, 5, 8192, 0.5, 24),        # one row per tile: every row pair is a seam
+    (3, 20, 1024, 0.3, 25),       # seams of tiles and of d0 planes
+    (1, 4, 16384, 0.5, 26)])      # rows longer than a tile: the general form
+def test_tile_and_seam_edges(H, n_d0, n_qpt, n_phi, density, seed):
+    spec = synth.grid_spec("c1_single_100trk")
+    spec.update(n_qpt=n_qpt, n_phi=n_phi, n_d0=n_d0, d0_lo_mm=-50.0, d0_hi_mm=50.0, threshold=1)
+    rng = np.random.default_rng(seed)
+    shape = (n_d0, n_qpt, n_phi)
+    events = [image_peaks(rng, shape, density), image_peaks(rng, shape, 0.05),
+              image_peaks(rng, shape, 1.0, all_cells=True), image_peaks(rng, shape, 0.9)]
+    events.insert(1, events[0][:0])
+    run_lists(H, spec, events, reps=2)
