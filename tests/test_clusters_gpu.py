@@ -346,3 +346,37 @@ def test_tile_and_seam_edges(H, n_d0, n_qpt, n_phi, density, seed):
               image_peaks(rng, shape, 1.0, all_cells=True), image_peaks(rng, shape, 0.9)]
     events.insert(1, events[0][:0])
     run_lists(H, spec, events, reps=2)
+
+
+@pytest.mark.parametrize("members,n_layers,b_tesla,rz", [
+    (4, 3, 3.8, False), (48, 10, 3.8, True), (64, 16, 3.8, False), (80, 7, 8.0, True), (300, 16, 8.0, True)])
+def test_fit_member_counts_and_angles(H, members, n_layers, b_tesla, rz):
+    # noise hits, `members` per cell on average: below, around and above the
+    # 64 scanned hits a fit keeps in registers; at 8 T the outer layers'
+    # azimuths reach past pi/4 from the reference (FIT_TOL as derived above)
+    import torch
+    spec = synth.grid_spec("c2_single_1ktrk_rz" if rz else "c1_single_100trk")
+    spec.update(n_layers=n_layers, layer_r_mm=list(np.linspace(60.0, 800.0, n_layers)), b_tesla=b_tesla,
+                n_qpt=6, n_phi=64, threshold=min(3, n_layers))
+    if rz:
+        spec.update(n_z0=16, n_cot=16)
+    tab = oracle.Tables(spec)
+    rng = np.random.default_rng(members)
+    evs = []
+    for n in (64 * members, 0, 32 * members + 7):
+        evs.append((rng.integers(0, n_layers, n).astype(np.uint8), rng.integers(0, 1 << 32, n, dtype=np.uint64)
+                    .astype(np.uint32), rng.integers(-1200000, 1200000, n).astype(np.int32)))
+    batch = synth.concat_events(evs)
+    E, cap = 3, 3 * tab.cells
+    ctx = H.HoughContext(spec, max_events=E, max_hits=batch.n_hits, max_peaks=cap)
+    hits = H.DeviceHits.from_batch(batch)
+    pk, poff = ctx.peaks(ctx.vote(hits), E, capacity=cap)
+    _, cl, coff = ctx.peak_clusters(pk, poff, E)
+    fits = ctx.cluster_fit(hits, pk, poff, cl, coff)
+    torch.cuda.synchronize()
+    for e in range(E):
+        ev = batch.event(e)
+        opk = oracle.peaks(tab, oracle.vote_mask(tab, ev.layer, ev.phi))
+        _, ocl = oracle.clusters(tab, opk)
+        want = oracle.fit(tab, ev.layer, ev.phi, opk, ocl, ev.z if rz else None)
+        check_fit(H, H.fits_numpy(fits, coff, e), want, what=f"event {e}")
