@@ -831,6 +831,362 @@ k_rz_vote_fast(RzParams P)
     }
 }
 
+// Dense form of the fast kernel, for events whose cells hold many members.
+// One workgroup of four waves per candidate: the member list is gathered
+// once, wave w counts cot bins 64 w .. 64 w + 63 (then + 256), one per lane.
+//
+// What bounds the one-wave form here: its counters and lists leave four
+// waves per compute unit, a wave walks its four passes one after another,
+// eight candidates per ticket spread badly over a short record list, and
+// every vote pays for the running maximum (the atomic's return value, five
+// more instructions).  Here a vote is one atomic without a return value; a
+// pass ends with one sweep over the lane's counters that takes the largest
+// count, two packed maxima per four counters, and clears them; the z0 bin
+// is found for the winning cot bin alone, from a histogram of its votes.
+// Counts are bytes: a pass sweeps (without clearing) before they could pass
+// 255, and a candidate whose count really does is left to k_rz_redo.
+// 16 events of 100 to 10,000 tracks (members 20 to 1100 per cell, 16,384
+// candidates): 733 -> 373 us; one event of 1000 tracks, 1024 candidates: 151
+// -> 26 us.
+constexpr uint32_t kDenseThreads = 256, kDenseWaves = kDenseThreads / 64;
+constexpr uint32_t kDenseList = 3072;         // scanned hits a candidate may have
+
+__host__ __device__ inline uint32_t rz_dense_rows(uint32_t n_z0) { return n_z0 / 4 + 1; }
+__host__ __device__ inline size_t rz_dense_lds(uint32_t n_z0)
+{
+    return size_t(kDenseWaves) * rz_dense_rows(n_z0) * 256 + size_t(kDenseList) * 4 +
+           size_t(n_z0) * 4;
+}
+
+__device__ __forceinline__ uint32_t pk_max16(uint32_t a, uint32_t b)
+{
+    typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2, a),
+                                                                  __builtin_bit_cast(u16x2, b)));
+}
+
+// The lowest set bit of m, cleared in m.
+__device__ __forceinline__ uint32_t take_bit(uint64_t &m)
+{
+    const uint32_t i = uint32_t(__builtin_ctzll(m));
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm("s_bitset0_b64 %0, %1" : "+s"(m) : "s"(i));
+#else
+    m &= m - 1;
+#endif
+    return i;
+}
+
+// One layer's window of scanned hits: hit = scan index + (scan index < split
+// ? add1 : add2) relative to the event, and the layer's offset at the row.
+struct RzWindow {
+    uint32_t add1, add2, split, o;
+};
+
+// MUL as in k_rz_vote_fast: 2 = 24-bit multiply-high, else 32-bit and shift.
+//
+// A candidate's loads are a chain (candidate index, peak record, row offset,
+// bucket bounds, hits); each link but the last is issued one step of the
+// loop, or the votes, ahead of its use.
+template <int MUL>
+__global__ void __launch_bounds__(kDenseThreads) k_rz_vote_dense(RzParams P)
+{
+    HOUGH_DYNAMIC_LDS(uint4, lds4);
+    uint32_t *lds = reinterpret_cast<uint32_t *>(lds4);
+    __shared__ RzWindow win_s[kMaxLayers];
+    __shared__ uint32_t cnt_s[kMaxLayers], start_s[kMaxLayers];
+    __shared__ uint32_t wave_cnt[kDenseWaves], wave_cot[kDenseWaves], wave_ovf[kDenseWaves], bin_s;
+    const uint32_t t = threadIdx.x, lane = t & 63;
+    const uint32_t wave = uni(t >> 6);
+    const uint32_t rows = rz_dense_rows(P.n_z0), full = P.n_z0 / 4;
+    uint32_t *col = lds + wave * rows * 64 + lane;            // this lane's counters: row stride 64 dwords
+    int32_t *list = reinterpret_cast<int32_t *>(lds + kDenseWaves * rows * 64);
+    uint32_t *hist = reinterpret_cast<uint32_t *>(list + kDenseList);
+    const uint32_t nl = P.n_layers, nb = 1u << P.bucket_bits, bsh = 32 - P.bucket_bits;
+    const uint32_t bytes_last = P.n_z0 % 4 ? (1u << (8 * (P.n_z0 % 4))) - 1u : 0u;   // real bins of the last row
+    const uint64_t total = min(P.roff[P.n_events], P.out_capacity), step = gridDim.x;
+    for (uint32_t r = 0; r < rows; ++r) col[r * 64] = 0;
+    for (uint32_t i = t; i < P.n_z0; i += kDenseThreads) hist[i] = 0;
+    auto bin_of = [&](uint32_t u) -> uint32_t {
+        if (MUL == 2) return mulhi_u24(P.bm, min(u, P.span24));
+        return min(uint32_t(__umulhi(u, P.bm)) >> P.bs, P.n_z0);
+    };
+    // the four links; indices past the last candidate stay on the last one
+    auto event_of = [&](uint64_t c, uint32_t e) {
+        while (e + 1 < P.n_events && P.roff[e + 1] <= c) ++e;
+        return uni(e);
+    };
+    auto index_of = [&](uint64_t c, uint32_t e) {
+        return P.cap ? P.cand[c] : uint32_t(c - P.roff[e]);
+    };
+    auto record_of = [&](uint32_t e, uint32_t pk) { return P.peaks[P.poff[e] + pk]; };
+    uint32_t o = 0, valid = 0;                  // lane l: layer l's offset at the row, whether it can hold members
+    auto load_row = [&](uint2 rec) {
+        o = 0;
+        valid = 0;
+        if (lane < nl && ((rec.y >> lane) & 1u)) {
+            const size_t ti = size_t(lane) * P.rows + (rec.x >> P.log2phi) % P.n_qpt;
+            valid = P.V[ti];
+            o = P.O[ti];
+        }
+    };
+    uint32_t len1 = 0, len2 = 0, hs1 = 0, hs2 = 0;
+    auto load_windows = [&](uint32_t e, uint2 rec) {
+        len1 = len2 = hs1 = hs2 = 0;
+        if (valid) {
+            const uint32_t start = o + ((rec.x & (P.nphi - 1)) << P.shift);
+            const uint32_t b0 = start >> bsh;
+            const uint64_t W = uint64_t(1) << P.shift, BW = uint64_t(1) << bsh;
+            const uint32_t nbk = min(uint32_t(((uint64_t(start) & (BW - 1)) + W - 1) / BW + 1), nb);
+            const uint32_t *bl = P.bucket_off + (size_t(e) * nl + lane) * (nb + 1);
+            const uint32_t e1 = b0 + nbk;
+            const bool wraps = e1 > nb;
+            hs1 = bl[b0];
+            const uint32_t end1 = bl[wraps ? nb : e1], first = bl[0], end2 = bl[wraps ? e1 - nb : 0];
+            len1 = end1 - hs1;
+            hs2 = first;
+            len2 = wraps ? end2 - first : 0u;
+        }
+    };
+    if (blockIdx.x >= total) return;
+    auto clamped = [&](uint64_t c) { return min(c, total - 1); };
+    uint64_t c = blockIdx.x;
+    uint32_t e0 = event_of(c, 0), pk0 = index_of(c, e0);
+    uint2 rec0 = record_of(e0, pk0);
+    load_row(rec0);
+    load_windows(e0, rec0);
+    uint32_t e1 = event_of(clamped(c + step), e0), pk1 = index_of(clamped(c + step), e1);
+    uint2 rec1 = record_of(e1, pk1);
+    uint32_t e2 = event_of(clamped(c + 2 * step), e1), pk2 = index_of(clamped(c + 2 * step), e2);
+    for (; c < total; c += step) {
+        const uint32_t cell = uni(rec0.x), pk = uni(pk0);
+        const uint32_t k = (cell >> P.log2phi) % P.n_qpt, p = cell & (P.nphi - 1);
+        const uint64_t eb = uni64(min(P.offs[e0], P.n_hits));
+        // this lane's first cot bin's (Z + z0_lo) of every layer, as in the fast kernel
+        const int32_t *zrow = P.Zl + size_t(k) * P.n_cot * kMaxLayers;
+        uint32_t zc[kMaxLayers];
+        auto load_rows = [&](uint32_t jj) {
+            const uint4 *q = reinterpret_cast<const uint4 *>(zrow + size_t(min(jj, P.n_cot - 1)) * kMaxLayers);
+#pragma unroll
+            for (uint32_t g = 0; g < kMaxLayers / 4; ++g) {
+                const uint4 v = q[g];
+                zc[4 * g] = v.x;
+                zc[4 * g + 1] = v.y;
+                zc[4 * g + 2] = v.z;
+                zc[4 * g + 3] = v.w;
+            }
+        };
+        load_rows(wave * 64 + lane);
+
+        const uint32_t len = len1 + len2;
+        uint32_t incl = len;
+        incl += uint32_t(__builtin_amdgcn_update_dpp(0, int(incl), 0x111, 0xF, 0xF, false));   // row_shr:1
+        incl += uint32_t(__builtin_amdgcn_update_dpp(0, int(incl), 0x112, 0xF, 0xF, false));   // row_shr:2
+        incl += uint32_t(__builtin_amdgcn_update_dpp(0, int(incl), 0x114, 0xF, 0xF, false));   // row_shr:4
+        incl += uint32_t(__builtin_amdgcn_update_dpp(0, int(incl), 0x118, 0xF, 0xF, false));   // row_shr:8
+        const uint32_t T = uint32_t(__builtin_amdgcn_readlane(int(incl), 15));
+        const bool fits = T <= kDenseList;
+        if (t < kMaxLayers) {
+            const uint32_t at = incl - len;
+            start_s[t] = at;
+            win_s[t] = RzWindow{hs1 - at, hs2 - at - len1, at + len1, o};
+            cnt_s[t] = 0;
+        }
+        if (t == 0) bin_s = 0xFFFFFFFFu;
+        __syncthreads();
+        // the scanned hits over the workgroup; a layer's members are packed
+        // from its window's place in the list, in any order (past the list's
+        // size they are counted)
+        constexpr uint32_t kU = 4;
+        for (uint32_t g0 = t; g0 < T; g0 += kU * kDenseThreads) {
+            uint32_t ph[kU], ls[kU], oo[kU];
+            int32_t zv[kU];
+#pragma unroll
+            for (uint32_t u = 0; u < kU; ++u) {
+                const uint32_t gi = g0 + u * kDenseThreads;
+                ls[u] = kMaxLayers;
+                ph[u] = oo[u] = 0;
+                zv[u] = 0;
+                if (gi < T) {
+                    uint32_t l = 0;
+#pragma unroll
+                    for (uint32_t d = 8; d > 0; d >>= 1) l += start_s[l + d] <= gi ? d : 0u;
+                    const RzWindow w = win_s[l];
+                    const uint64_t h = eb + (gi + (gi < w.split ? w.add1 : w.add2));
+                    ph[u] = P.phi[h];
+                    zv[u] = P.z[h];
+                    oo[u] = w.o;
+                    ls[u] = l;
+                }
+            }
+#pragma unroll
+            for (uint32_t u = 0; u < kU; ++u) {
+                if (ls[u] < kMaxLayers && ((ph[u] - oo[u]) >> P.shift) == p) {
+                    const uint32_t pos = atomicAdd(&cnt_s[ls[u]], 1u);
+                    if (fits) list[start_s[ls[u]] + pos] = zv[u];
+                }
+            }
+        }
+        __syncthreads();
+        // ahead: the next candidate's row, the record of the one after it
+        // and the index of the one after that
+        load_row(rec1);
+        const uint2 rec2 = record_of(e2, pk2);
+        const uint32_t e3 = event_of(clamped(c + 3 * step), e2), pk3 = index_of(clamped(c + 3 * step), e3);
+
+        uint32_t best_c = 0, best_j = 0;       // uniform over the wave
+        bool ovf = !fits;
+        if (fits) {
+            for (uint32_t j0 = wave * 64; j0 < P.n_cot; j0 += kDenseThreads) {
+                if (j0 != wave * 64) load_rows(j0 + lane);
+                uint32_t room = 255;                          // votes before a count could pass 255
+                uint32_t m1 = 0, m2 = 0;
+                auto sweep = [&](bool clear) {
+                    uint32_t r0 = 0;
+                    for (; r0 + 8 <= full; r0 += 8) {
+                        uint32_t x[8];
+#pragma unroll
+                        for (uint32_t i = 0; i < 8; ++i) x[i] = col[(r0 + i) * 64];
+                        if (clear) {
+#pragma unroll
+                            for (uint32_t i = 0; i < 8; ++i) col[(r0 + i) * 64] = 0;
+                        }
+#pragma unroll
+                        for (uint32_t i = 0; i < 8; ++i) {
+                            m1 = pk_max16(m1, x[i]);                       // the high bytes decide
+                            m2 = pk_max16(m2, (x[i] & 0x00FF00FFu));       // the low bytes
+                        }
+                    }
+                    for (; r0 < full; ++r0) {
+                        const uint32_t x = col[r0 * 64];
+                        if (clear) col[r0 * 64] = 0;
+                        m1 = pk_max16(m1, x);
+                        m2 = pk_max16(m2, x & 0x00FF00FFu);
+                    }
+                    if (bytes_last) {                         // the trash bin shares this row
+                        const uint32_t x = col[full * 64] & bytes_last;
+                        m1 = pk_max16(m1, x);
+                        m2 = pk_max16(m2, x & 0x00FF00FFu);
+                    }
+                    if (clear) col[full * 64] = 0;
+                };
+                auto lane_max = [&]() {
+                    const uint32_t hi = max((m1 >> 8) & 0xFFu, m1 >> 24), lo = max(m2 & 0xFFFFu, m2 >> 16);
+                    return max(hi, lo);
+                };
+                uint32_t n = uni(cnt_s[0]), at = uni(start_s[0]);
+                int32_t znext = lane < n ? list[at + lane] : 0;       // the next layer's first members, read ahead
+                for (uint32_t l = 0; l < nl; ++l) {
+                    const uint32_t nc = n, ac = at;
+                    int32_t z = znext;
+                    if (l + 1 < nl) {
+                        n = uni(cnt_s[l + 1]);
+                        at = uni(start_s[l + 1]);
+                        znext = lane < n ? list[at + lane] : 0;
+                    }
+                    const uint32_t zl = zc[l];
+                    // (Z + z0_lo) is monotone in the cot bin: its range over the pass
+                    const int32_t za = __builtin_amdgcn_readlane(int(zl), 0), zb = __builtin_amdgcn_readlane(int(zl), 63);
+                    const int32_t mn = min(za, zb), mx = max(za, zb);
+                    for (uint32_t g0 = 0; g0 < nc; g0 += 64) {
+                        if (g0) z = g0 + lane < nc ? list[ac + g0 + lane] : 0;
+                        const bool act = g0 + lane < nc && z >= mn && (z < mx || uint64_t(uint32_t(z - mx)) < P.span);
+                        uint64_t bal = __ballot(act);
+                        uint32_t nq = uint32_t(__popcll(bal));
+                        if (nq > room) {
+                            sweep(false);
+                            room = 255u - wave_max_u32(lane_max());
+                            if (nq > room) { ovf = true; break; }
+                        }
+                        room -= nq;
+                        auto votes = [&](auto qc) {
+                            constexpr uint32_t Q = decltype(qc)::value;
+                            uint32_t b[Q];
+#pragma unroll
+                            for (uint32_t q = 0; q < Q; ++q)
+                                b[q] = bin_of(uint32_t(__builtin_amdgcn_readlane(z, int(take_bit(bal)))) - zl);
+#pragma unroll
+                            for (uint32_t q = 0; q < Q; ++q)
+                                __hip_atomic_fetch_add(col + (b[q] >> 2) * 64, 1u << ((b[q] << 3) & 31u),
+                                                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                        };
+                        for (; nq >= 4; nq -= 4) votes(std::integral_constant<uint32_t, 4>{});
+                        for (; nq; --nq) votes(std::integral_constant<uint32_t, 1>{});
+                    }
+                    if (ovf) break;
+                }
+                m1 = 0;
+                m2 = 0;
+                sweep(true);
+                const uint32_t mine = j0 + lane < P.n_cot ? lane_max() : 0u;
+                const uint32_t most = wave_max_u32(mine);
+                if (most > best_c) {
+                    best_c = most;
+                    best_j = j0 + uint32_t(__ffsll(static_cast<unsigned long long>(__ballot(mine == most)))) - 1;
+                }
+                if (ovf) break;
+            }
+        }
+        load_windows(e1, rec1);
+        if (lane == 0) {
+            wave_cnt[wave] = best_c;
+            wave_cot[wave] = best_j;
+            wave_ovf[wave] = ovf;
+        }
+        __syncthreads();
+        uint32_t nm = 0, any_ovf = 0;
+        best_c = 0;
+        best_j = 0xFFFFFFFFu;
+        for (uint32_t l = 0; l < nl; ++l) nm += cnt_s[l];
+        for (uint32_t w = 0; w < kDenseWaves; ++w) {
+            const uint32_t x = wave_cnt[w], j = wave_cot[w];
+            any_ovf |= wave_ovf[w];
+            if (x > best_c || (x == best_c && j < best_j)) {
+                best_c = x;
+                best_j = j;
+            }
+        }
+        if (best_c == 0) best_j = 0;
+        if (!any_ovf && best_c != 0) {         // uniform over the workgroup
+            // the votes of cot bin best_j: its smallest bin with best_c of them
+            for (uint32_t l = wave; l < nl; l += kDenseWaves) {
+                const uint32_t n = cnt_s[l], at = start_s[l];
+                const uint32_t zl = uint32_t(zrow[size_t(best_j) * kMaxLayers + l]);
+                for (uint32_t i = lane; i < n; i += 64) {
+                    const uint32_t b = bin_of(uint32_t(list[at + i]) - zl);
+                    if (b < P.n_z0) atomicAdd(&hist[b], 1u);
+                }
+            }
+            __syncthreads();
+            for (uint32_t b = t; b < P.n_z0; b += kDenseThreads) {
+                if (hist[b] == best_c) atomicMin(&bin_s, b);
+                hist[b] = 0;
+            }
+            __syncthreads();
+        }
+        if (t == 0) {
+            if (any_ovf) {
+                P.out4[2 * c] = make_uint2(pk, 0u);
+                P.out4[2 * c + 1] = make_uint2(kRzRedo, nm);
+                const uint32_t i = atomicAdd(P.redo_count, 1u);
+                if (i < P.redo_cap) P.redo_list[i] = c;
+            } else {
+                P.out4[2 * c] = make_uint2(pk, best_c ? best_j | (bin_s << 16) : 0u);
+                P.out4[2 * c + 1] = make_uint2(best_c, nm);
+            }
+        }
+        __syncthreads();                       // the list, the counts and bin_s are reused
+        e0 = e1;
+        pk0 = pk1;
+        rec0 = rec1;
+        e1 = e2;
+        pk1 = pk2;
+        rec1 = rec2;
+        e2 = e3;
+        pk2 = pk3;
+    }
+}
+
 // The exact path for the records k_rz_vote_fast marked (count == kRzRedo):
 // the wave takes every gridDim-th entry of the list of marked records the
 // fast kernel appended (when they all fit it; otherwise it scans every
@@ -1252,8 +1608,16 @@ hipError_t launch_rz(hough_ctx *c, const hough_hits *h, const hough_peak *peaks,
         while (mcap > 256 && size_t(rz_fast_lds_dwords(hw, mcap)) * 4 > c->max_lds) mcap >>= 1;
     }
     const size_t fast_lds = size_t(rz_fast_lds_dwords(hw, mcap)) * 4;
+    // Cells of many members go to the dense form: from 48 members per cell
+    // on.  Its list is by scanned hits, so it wants the azimuth
+    // buckets narrower than a cell (n_phi <= 2048), and two workgroups per
+    // compute unit.  Any rz knob set by hand keeps the one-wave form.
+    const size_t dense_lds = rz_dense_lds(g.n_z0);
+    const bool dense = c->rz_fast && !c->tun.rz_slow_path && !c->tun.rz_counter_bits && !c->tun.rz_waves_per_cu &&
+                       !c->tun.rz_member_cap && per_cell >= 48.0 && c->bucket_bits > c->log2_phi &&
+                       dense_lds + 512 <= c->max_lds_rank;
     // the fast kernel pads member lists with a spare layer (n_layers < 16)
-    if (c->rz_fast && !c->tun.rz_slow_path && fast_lds <= c->max_lds && g.n_layers < kMaxLayers) {
+    if (dense || (c->rz_fast && !c->tun.rz_slow_path && fast_lds <= c->max_lds && g.n_layers < kMaxLayers)) {
         P.hw = hw;
         P.mcap = mcap;
         // one queue per XCD where the records can give every wave several
@@ -1266,7 +1630,14 @@ hipError_t launch_rz(hough_ctx *c, const hough_hits *h, const hough_peak *peaks,
         prof_begin(c, "rz_vote", s, &t);
         const int mul = P.bs != 0 ? 1 : (P.span < (1u << 24) && P.bm < (1u << 24)) ? 2 : 0;
         P.span24 = uint32_t(P.span);
-        if (bits == 4)
+        if (dense) {
+            const uint32_t wgs = uint32_t(std::max<uint64_t>(
+                1, std::min<uint64_t>(rz_records_bound(c, h, peak_capacity, capacity), uint64_t(c->n_cu) * 2)));
+            if (mul == 2)
+                hipLaunchKernelGGL(k_rz_vote_dense<2>, dim3(wgs), dim3(kDenseThreads), dense_lds, s, P);
+            else
+                hipLaunchKernelGGL(k_rz_vote_dense<0>, dim3(wgs), dim3(kDenseThreads), dense_lds, s, P);
+        } else if (bits == 4)
             launch_fast<4>(mul, blocks, fast_lds, s, P);
         else if (bits == 8)
             launch_fast<8>(mul, blocks, fast_lds, s, P);

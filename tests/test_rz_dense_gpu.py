@@ -1,0 +1,66 @@
+"""The rz form for cells of many members (chosen from 48 hits per cell on)
+against the oracle, bit for bit: pass remainders in the cot and z0 bins,
+layer counts, lists past their size, byte counts that pass 255, mid-pass
+sweeps, an empty event and the wide multiply-high."""
+import math
+
+import numpy as np
+import pytest
+
+import oracle
+import synth
+from test_gpu_parity import H, check_event, run_gpu, small_spec  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+
+def noise_event(rng, n, n_layers=10):
+    return (rng.integers(0, n_layers, n).astype(np.uint8), rng.integers(0, 1 << 32, n, dtype=np.uint64).astype(np.uint32),
+            rng.integers(-1_200_000, 1_200_000, n).astype(np.int32))
+
+
+def check(H, spec, events):
+    batch = synth.concat_events(events)
+    assert batch.n_hits / batch.n_events / spec["n_phi"] >= 48
+    res = run_gpu(H, spec, batch)
+    tab = oracle.Tables(spec)
+    for e in range(batch.n_events):
+        check_event(H, tab, res, batch, e, rz=True)
+    return res, batch
+
+
+@pytest.mark.parametrize("sizes,kw", [
+    ([2400, 0, 1600, 900], dict(n_phi=16, n_qpt=6)),                       # 56 to 150 members
+    ([2400, 1600], dict(n_phi=16, n_qpt=6, n_cot=70, n_z0=253)),           # ragged passes and counter rows
+    ([2400, 1600], dict(n_phi=16, n_qpt=6, n_cot=300, n_z0=10)),           # a second round of passes
+    ([2400, 1600], dict(n_phi=16, n_qpt=6, n_cot=1, n_z0=1)),
+    ([2400, 1600], dict(n_phi=16, n_qpt=6, cot_lo=1.2, cot_hi=-1.2)),      # Z decreasing
+    ([4000, 3000], dict(n_phi=4, n_qpt=4, n_cot=64)),                      # passes past 255 votes
+    ([9000, 100], dict(n_phi=2, n_qpt=3, n_cot=33)),                       # more scanned hits than the list holds
+    ([2400], dict(n_phi=16, n_qpt=6, z0_lo_um=-20_000_000, z0_hi_um=20_000_000)),   # 32-bit multiply-high
+])
+def test_dense_rz(H, sizes, kw):  # noqa: F811
+    rng = np.random.default_rng(sum(sizes))
+    check(H, small_spec(**kw), [noise_event(rng, n) for n in sizes])
+
+
+@pytest.mark.parametrize("n_layers", [1, 3, 15])
+def test_dense_rz_layer_counts(H, n_layers):  # noqa: F811
+    spec = small_spec(n_phi=16, n_qpt=6)
+    spec.update(n_layers=n_layers, layer_r_mm=list(np.linspace(60.0, 800.0, n_layers)), threshold=1)
+    rng = np.random.default_rng(n_layers)
+    check(H, spec, [noise_event(rng, n, n_layers) for n in (1700, 800)])
+
+
+@pytest.mark.parametrize("copies", [24, 26])
+def test_dense_rz_counts_around_255(H, copies):  # noqa: F811
+    # identical bin-centre tracks: 10 members per copy in one (cot, z0) bin
+    spec = small_spec(n_phi=16, n_qpt=41)
+    K, N = spec["n_qpt"], spec["n_phi"]
+    kap = spec["qpt_lo"] + (np.arange(K) + 0.5) * (spec["qpt_hi"] - spec["qpt_lo"]) / K
+    layer, phi, z = synth.track_hits(kap[20], (7 + 0.5) / N * 2 * math.pi,
+                                     cot=-1.2 + 160.5 * 2.4 / 256, z0=-200.0 + 140.5 * 400.0 / 256)
+    nl, nphi, nz = noise_event(np.random.default_rng(3), 800)
+    res, _ = check(H, spec, [(np.concatenate([layer] * copies + [nl]), np.concatenate([phi] * copies + [nphi]),
+                              np.concatenate([z] * copies + [nz]))])
+    assert H.rz_numpy(res["rz"], res["roff"], 0)["count"].max() >= 10 * copies
