@@ -46,11 +46,12 @@ bool dev_alloc(T **p, size_t count)
 
 void free_all(hough_ctx *c)
 {
-    void *ptrs[] = {c->d_O, c->d_V, c->d_Z, c->d_Zl, c->d_rk_info, c->d_rk_sorted, c->d_phi_a, c->d_z_a, c->d_phi_b, c->d_z_b,
+    void *ptrs[] = {c->d_O, c->d_V, c->d_Z, c->d_Zl, c->d_rk_info, c->d_rk_sorted, c->d_phi_a, c->d_hit_b,
                     c->d_layer_off, c->d_bucket_off, c->d_order, c->d_counters, c->d_tile_counts,
                     c->d_tile_off, c->d_cand, c->d_cand_counts, c->d_rz_hist, c->d_redo_list, c->d_gap_info, c->d_gap_list,
                     c->d_scan_part, c->d_scan_off, c->d_dir_tab, c->d_cl_rank, c->d_cl_part,
-                    c->d_cl_part_off, c->d_part_cnt, c->d_part_base};
+                    c->d_cl_part_off, c->d_part_cnt, c->d_part_base,
+                    c->d_sec_part, c->d_sec_off};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
     for (auto &t : c->pending) {
@@ -252,8 +253,8 @@ int hough_create(const hough_grid_spec *spec, const hough_limits *limits, int de
     const size_t rzh = rz ? size_t(c->n_cu) * kMaxRzWavesPerCu * spec->n_z0 : 0;
     bool ok = dev_alloc(&c->d_O, nOV + kOPad) && dev_alloc(&c->d_V, nOV) && dev_alloc(&c->d_Z, Z.size()) &&
               dev_alloc(&c->d_Zl, Zl.size()) &&
-              dev_alloc(&c->d_phi_a, H) && dev_alloc(&c->d_z_a, rz ? H : 0) &&
-              dev_alloc(&c->d_phi_b, buckets ? H : 0) && dev_alloc(&c->d_z_b, rz ? H : 0) &&
+              dev_alloc(&c->d_phi_a, rz ? 2 * H : H) &&
+              dev_alloc(&c->d_hit_b, rz ? 2 * H : buckets ? H : 0) &&
               dev_alloc(&c->d_layer_off, size_t(E) * (L + 1)) &&
               dev_alloc(&c->d_bucket_off, size_t(E) * L * nb) && dev_alloc(&c->d_order, E) &&
               dev_alloc(&c->d_counters, kCounterDwords) && dev_alloc(&c->d_tile_counts, c->n_peak_tiles) &&
@@ -262,6 +263,8 @@ int hough_create(const hough_grid_spec *spec, const hough_limits *limits, int de
               dev_alloc(&c->d_redo_list, rz ? kRedoListCap : 0) &&
               dev_alloc(&c->d_part_cnt, c->max_parts * kSplitBins) &&
               dev_alloc(&c->d_part_base, c->max_parts * kSplitBins) &&
+              dev_alloc(&c->d_sec_part, buckets ? (uint64_t(E) + uint64_t(kIndexPartsPerCu) * c->n_cu) * kSectorBins : 0) &&
+              dev_alloc(&c->d_sec_off, buckets ? size_t(E) * (kSectorBins + 1) : 0) &&
               dev_alloc(&c->d_gap_info, size_t(E) * L) && dev_alloc(&c->d_gap_list, H) &&
               dev_alloc(&c->d_scan_part, c->scan_blocks_max) && dev_alloc(&c->d_scan_off, c->scan_blocks_max + 1) &&
               dev_alloc(&c->d_dir_tab, size_t(E) * L * spec->n_phi) &&
@@ -405,7 +408,7 @@ int hough_cluster_fit(hough_ctx *ctx, const hough_hits *hits, const hough_peak *
         return HOUGH_EINVAL;
     // the member search reads the (layer, azimuth bucket) index, which the
     // context keeps only with an rz grid or limits.max_peaks > 0
-    if (ctx->bucket_bits == 0 || !ctx->d_phi_b || !ctx->d_bucket_off) return HOUGH_EINVAL;
+    if (ctx->bucket_bits == 0 || !ctx->d_hit_b || !ctx->d_bucket_off) return HOUGH_EINVAL;
     if (hits->n_events > ctx->lim.max_events || hits->n_hits > ctx->lim.max_hits) return HOUGH_ELIMIT;
     DeviceGuard guard(ctx->device);
     const hipError_t e = launch_fit(ctx, hits, peaks, peak_capacity, event_peak_offsets, clusters, capacity,

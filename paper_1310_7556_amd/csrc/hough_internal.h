@@ -4,6 +4,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstddef>
 #include <cstdint>
 #include <string>
@@ -67,10 +68,9 @@ struct hough_ctx {
     uint32_t rz_magic_m = 0, rz_magic_s = 0;
 
     // scratch (device)
-    uint32_t *d_phi_a = nullptr;     // [max_hits] hits grouped by layer
-    int32_t *d_z_a = nullptr;        // [max_hits]
-    uint32_t *d_phi_b = nullptr;     // [max_hits] grouped by (layer, bucket) for rz
-    int32_t *d_z_b = nullptr;        // [max_hits]
+    uint32_t *d_phi_a = nullptr;     // [max_hits] hits grouped by layer; with an rz stage twice as many
+                                     // entries, the hit index's intermediate records
+    uint32_t *d_hit_b = nullptr;     // [max_hits] hits by (layer, bucket): phi, or {phi, z} with an rz stage
     uint32_t *d_layer_off = nullptr; // [max_events][L + 1] relative to the event start
     uint32_t *d_bucket_off = nullptr;// [max_events][L][NB + 1]
     uint32_t *d_order = nullptr;     // [max_events] events, longest first
@@ -84,6 +84,8 @@ struct hough_ctx {
     uint32_t *d_part_cnt = nullptr;    // [parts][kSplitBins] per-part counts
     uint32_t *d_part_base = nullptr;   // [parts][kSplitBins] per-part starts
     uint64_t max_parts = 0;
+    uint32_t *d_sec_part = nullptr;    // [parts][kSectorBins] hit index: counts, then places, per part
+    uint32_t *d_sec_off = nullptr;     // [max_events][kSectorBins + 1] hit index: starts per (layer, sector)
     uint32_t *d_rz_hist = nullptr;     // [rz blocks][n_z0] zeroed uint32 (rz slow path)
     uint64_t *d_redo_list = nullptr;   // [kRedoListCap] records the fast rz kernel leaves to the exact path
     uint4 *d_gap_info = nullptr;       // [max_events][L] gap vote: {mode, entries, list start, 0}
@@ -120,8 +122,8 @@ void prof_end(hough_ctx *c, hipStream_t s, KernelTimer *t);
 
 // ---- launchers (each returns the HIP status of its launch) --------------
 hipError_t launch_fill_u32(hough_ctx *c, uint32_t *p, uint32_t v, size_t n, hipStream_t s);
-hipError_t launch_bucket_layers(hough_ctx *c, const hough_hits *h, bool with_z, hipStream_t s);
-hipError_t launch_bucket_phi(hough_ctx *c, const hough_hits *h, hipStream_t s, bool with_z = true);
+hipError_t launch_bucket_layers(hough_ctx *c, const hough_hits *h, hipStream_t s);
+hipError_t launch_hit_index(hough_ctx *c, const hough_hits *h, bool with_z, hipStream_t s);
 hipError_t launch_event_order(hough_ctx *c, const hough_hits *h, hipStream_t s);
 hipError_t launch_vote(hough_ctx *c, const hough_hits *h, uint16_t *acc, hipStream_t s);
 hipError_t launch_vote_count(hough_ctx *c, const hough_hits *h, uint32_t *counts, hipStream_t s);
@@ -152,11 +154,22 @@ hipError_t launch_peaks_rows_pass(hough_ctx *c, bool write, const uint16_t *acc,
 constexpr uint32_t kSplitPartsPerCu = 4;
 constexpr uint32_t kSplitMaxParts = 64;
 constexpr uint32_t kSplitBins = 17;      // layers (<= 16) or popcount levels 0..16
+constexpr uint32_t kSectorBits = 4;      // hit index: 16 azimuth sectors per layer
+constexpr uint32_t kSectorBins = 16u << kSectorBits;
+// Parts per event of the hit index's split form: about kIndexPartsPerCu per
+// compute unit in all (E * K <= E + kIndexPartsPerCu * n_cu), of at least
+// kIndexPartHits hits on average.
+constexpr uint32_t kIndexPartsPerCu = 8, kIndexPartHits = 1024;
 inline uint32_t split_parts(const hough_ctx *c, uint32_t E)
 {
     if (E == 0 || E >= 2u * uint32_t(c->n_cu) || !c->d_part_cnt) return 0;
     const uint32_t K = (kSplitPartsPerCu * uint32_t(c->n_cu) + E - 1) / E;
     return K < 2 ? 0 : (K > kSplitMaxParts ? kSplitMaxParts : K);
+}
+inline uint32_t index_parts(const hough_ctx *c, uint32_t E, uint64_t n_hits)
+{
+    const uint64_t fill = (kIndexPartsPerCu * uint64_t(c->n_cu) + E - 1) / E, most = n_hits / E / kIndexPartHits;
+    return uint32_t(std::max<uint64_t>(1, std::min<uint64_t>(fill, most)));
 }
 // The split forms' plan pass (k_bucket.hip): per event, the start of each of
 // n_bins bins and each part's first position per bin (bin_off may be null).

@@ -34,8 +34,8 @@ namespace hough {
 namespace {
 
 struct FitParams {
-    const uint32_t *phi_b;        // hits grouped by (layer, azimuth bucket) per event
-    const int32_t *z_b;           // their z (um), or null: no longitudinal fit
+    const uint32_t *hit;          // hits by (layer, azimuth bucket) per event: phi, or with the
+                                  // longitudinal fit {phi, z (um)}
     const uint32_t *bucket_off;   // [E][L][NB + 1] relative to the event start
     uint32_t bucket_bits;
     const uint64_t *hoff;         // [E + 1] hit offsets
@@ -123,7 +123,7 @@ struct LayerWindow {
 constexpr uint32_t kFitThreads = 256, kFitRows = kFitThreads / 16;
 constexpr uint32_t kFitKept = 4;          // scanned hits per lane kept between the passes
 
-// Z: the longitudinal line is fitted too (P.z_b set); a separate instance
+// Z: the longitudinal line is fitted too; a separate instance
 // keeps the transverse-only kernel's register count (and occupancy) down.
 template <bool Z>
 __global__ void __launch_bounds__(kFitThreads) k_fit(FitParams P)
@@ -143,6 +143,7 @@ __global__ void __launch_bounds__(kFitThreads) k_fit(FitParams P)
     const double turn_rad = two_pi / 4294967296.0;
     const uint32_t pmask = P.n_phi - 1;
     const uint32_t nb = 1u << P.bucket_bits, bs = 32 - P.bucket_bits;
+    auto hit_at = [&](uint64_t h) { return Z ? reinterpret_cast<const uint2 *>(P.hit)[h] : make_uint2(P.hit[h], 0u); };
     uint32_t e = 0;
     // whole waves step together; the rows past the last cluster do nothing
     for (uint64_t c0 = uint64_t(blockIdx.x) * kFitRows + (row & ~3u); c0 < n_cl; c0 += uint64_t(gridDim.x) * kFitRows) {
@@ -228,8 +229,9 @@ __global__ void __launch_bounds__(kFitThreads) k_fit(FitParams P)
                     const uint32_t l = layer_of(gi);
                     const LayerWindow w = win[l];
                     const uint64_t h = eb + (gi + (gi < w.split ? w.add1 : w.add2));
-                    ph[i] = P.phi_b[h];
-                    if (Z) zi[i] = P.z_b[h];
+                    const uint2 ht = hit_at(h);
+                    ph[i] = ht.x;
+                    zi[i] = int32_t(ht.y);
                     oo[i] = w.o;
                     kl[i] = l;
                 }
@@ -258,12 +260,13 @@ __global__ void __launch_bounds__(kFitThreads) k_fit(FitParams P)
                 const uint32_t l = layer_of(gi);
                 const LayerWindow w = win[l];
                 const uint64_t h = eb + (gi + (gi < w.split ? w.add1 : w.add2));
-                const uint32_t ph = P.phi_b[h];
+                const uint2 ht = hit_at(h);
+                const uint32_t ph = ht.x;
                 if (((ph - w.o) >> P.shift) != p) continue;
                 double sa, ca;
                 turn_sincos(int32_t(ph - ref), sa, ca);
                 const double r = r_s[l];
-                visit(l, r * ca, r * sa, Z ? double(P.z_b[h]) * 1e-3 : 0.0);
+                visit(l, r * ca, r * sa, Z ? double(int32_t(ht.y)) * 1e-3 : 0.0);
             }
         };
         double sxx = 0, sxw = 0, sww = 0, sxy = 0, syw = 0;
@@ -368,12 +371,10 @@ hipError_t launch_fit(hough_ctx *c, const hough_hits *h, const hough_peak *peaks
     if (h->n_events == 0 || capacity == 0) return hipSuccess;
     // the longitudinal line needs z, bucketed with the azimuths (rz grids)
     const bool with_z = c->spec.n_z0 > 0 && h->z_um != nullptr;
-    hipError_t err = launch_bucket_layers(c, h, with_z, s);
-    if (err == hipSuccess) err = launch_bucket_phi(c, h, s, with_z);
+    const hipError_t err = launch_hit_index(c, h, with_z, s);
     if (err != hipSuccess) return err;
     FitParams P{};
-    P.phi_b = c->d_phi_b;
-    P.z_b = with_z ? c->d_z_b : nullptr;
+    P.hit = c->d_hit_b;
     P.bucket_off = c->d_bucket_off;
     P.bucket_bits = c->bucket_bits;
     P.hoff = h->event_offsets;

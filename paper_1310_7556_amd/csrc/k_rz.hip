@@ -41,8 +41,7 @@
 namespace hough {
 
 struct RzParams {
-    const uint32_t *phi;          // hits grouped by (layer, bucket)
-    const int32_t *z;
+    const uint2 *hit;             // {phi, z} of the hits by (layer, bucket)
     const uint64_t *offs;
     uint64_t n_hits;
     const uint32_t *bucket_off;   // [E][L][NB + 1]
@@ -184,7 +183,7 @@ __device__ __forceinline__ void for_members(const RzParams &P, uint64_t eb, cons
             const uint32_t bk = (b0 + i) & (nb - 1);
             const uint32_t hs = bl[bk], he = bl[bk + 1];
             for (uint32_t h = hs; h < he; ++h) {
-                const uint32_t ph = P.phi[eb + h];
+                const uint32_t ph = P.hit[eb + h].x;
                 if (((ph - o) >> P.shift) == p) fn(h, l);
             }
         }
@@ -207,7 +206,7 @@ __device__ void rz_slow(const RzParams &P, uint64_t eb, const uint32_t *bo, uint
             for_members(P, eb, bo, k, p, mask, [&](uint32_t h, uint32_t l) {
                 if ((seen++ & 63u) != lane) return;
                 const int64_t zl = int64_t(P.Z[(size_t(k) * P.n_layers + l) * P.n_cot + j]) + P.z0_lo;
-                const int32_t b = z0_bin(P, P.z[eb + h], zl);
+                const int32_t b = z0_bin(P, int32_t(P.hit[eb + h].y), zl);
                 if (b < 0) return;
                 if (pass == 0) {
                     atomicAdd(&g[b], 1u);
@@ -370,7 +369,7 @@ __global__ void __launch_bounds__(64) k_rz_vote(RzParams P)
                 for_members(P, r.eb, r.bo, k, p, mask, [&](uint32_t h, uint32_t l) {
                     if (!jv) return;
                     const int64_t zl = int64_t(P.Z[(size_t(k) * P.n_layers + l) * P.n_cot + j]) + P.z0_lo;
-                    const int32_t b = z0_bin(P, P.z[r.eb + h], zl);
+                    const int32_t b = z0_bin(P, int32_t(P.hit[r.eb + h].y), zl);
                     if (b < 0) return;
                     const uint32_t idx = uint32_t(b) * 64 + lane;
                     const uint32_t cnt = uint32_t(hist[idx]) + 1;
@@ -380,7 +379,7 @@ __global__ void __launch_bounds__(64) k_rz_vote(RzParams P)
                 for_members(P, r.eb, r.bo, k, p, mask, [&](uint32_t h, uint32_t l) {
                     if (!jv) return;
                     const int64_t zl = int64_t(P.Z[(size_t(k) * P.n_layers + l) * P.n_cot + j]) + P.z0_lo;
-                    const int32_t b = z0_bin(P, P.z[r.eb + h], zl);
+                    const int32_t b = z0_bin(P, int32_t(P.hit[r.eb + h].y), zl);
                     if (b >= 0) hist[uint32_t(b) * 64 + lane] = 0;
                 });
                 if (jv && bc > best_c) { best_c = bc; best_j = j; best_b = bb; }
@@ -544,8 +543,9 @@ k_rz_vote_fast(RzParams P)
                 const uint32_t l1 = lay[16 + ls];
                 const uint32_t h = local < l1 ? lay[32 + ls] + local : lay[48 + ls] + (local - l1);
                 // z is loaded with phi (not after the test) to save a round trip
-                const uint32_t ph = P.phi[r.eb + h];
-                const int32_t zh = P.z[r.eb + h];
+                const uint2 ht = P.hit[r.eb + h];
+                const uint32_t ph = ht.x;
+                const int32_t zh = int32_t(ht.y);
                 is_m = ((ph - lay[64 + ls]) >> P.shift) == p;
                 zv = is_m ? zh : 0;
             }
@@ -1013,8 +1013,9 @@ __global__ void __launch_bounds__(kDenseThreads) k_rz_vote_dense(RzParams P)
                     for (uint32_t d = 8; d > 0; d >>= 1) l += start_s[l + d] <= gi ? d : 0u;
                     const RzWindow w = win_s[l];
                     const uint64_t h = eb + (gi + (gi < w.split ? w.add1 : w.add2));
-                    ph[u] = P.phi[h];
-                    zv[u] = P.z[h];
+                    const uint2 ht = P.hit[h];
+                    ph[u] = ht.x;
+                    zv[u] = int32_t(ht.y);
                     oo[u] = w.o;
                     ls[u] = l;
                 }
@@ -1206,7 +1207,7 @@ __device__ void rz_exact_lds(const RzParams &P, const RzCand &r, int32_t *mz, ui
     uint32_t seen = 0;
     for_members(P, r.eb, r.bo, r.k, r.p, r.mask, [&](uint32_t h, uint32_t l) {
         if ((seen & 63u) == lane) {
-            mz[seen] = P.z[r.eb + h];
+            mz[seen] = int32_t(P.hit[r.eb + h].y);
             ml[seen] = uint8_t(l);
         }
         ++seen;
@@ -1510,8 +1511,7 @@ hipError_t launch_rz(hough_ctx *c, const hough_hits *h, const hough_peak *peaks,
     hipError_t err;
     const hough_grid_spec &g = c->spec;
     const uint32_t E = h->n_events;
-    if ((err = launch_bucket_layers(c, h, true, s)) != hipSuccess) return err;
-    if ((err = launch_bucket_phi(c, h, s)) != hipSuccess) return err;
+    if ((err = launch_hit_index(c, h, true, s)) != hipSuccess) return err;
     KernelTimer t;
     const bool fused = E <= kRzOffsetsMaxEvents;
     prof_begin(c, "rz_counts", s, &t);
@@ -1548,8 +1548,7 @@ hipError_t launch_rz(hough_ctx *c, const hough_hits *h, const hough_peak *peaks,
         return err;
 
     RzParams P;
-    P.phi = c->d_phi_b;
-    P.z = c->d_z_b;
+    P.hit = reinterpret_cast<const uint2 *>(c->d_hit_b);
     P.offs = h->event_offsets;
     P.n_hits = h->n_hits;
     P.bucket_off = c->d_bucket_off;

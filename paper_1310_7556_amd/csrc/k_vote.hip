@@ -149,7 +149,7 @@ hipError_t launch_vote_hits(hough_ctx *c, const hough_hits *h, void *out, hipStr
             return err;
         }
     }
-    if ((err = launch_bucket_layers(c, h, false, s)) != hipSuccess) return err;
+    if ((err = launch_bucket_layers(c, h, s)) != hipSuccess) return err;
     KernelTimer t;
     if (!lds) {
         const size_t words = size_t(h->n_events) * c->cells / (COUNT ? 1 : 2);
