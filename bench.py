@@ -169,10 +169,12 @@ def percentiles(ms):
                 p90=round(float(np.percentile(ms, 90)), 5), n=int(ms.size))
 
 
-# Algorithmic HBM bytes of the peak kernels: the count pass reads every
-# cell once; the write pass reads every cell again and writes each 8-byte
-# peak record.
+# Algorithmic HBM bytes of the peak kernels: the one-launch form reads every
+# cell once and writes each 8-byte peak record; of the two-pass forms the
+# count pass reads every cell, and the write pass reads it again and writes
+# the records.
 PEAK_KERNEL_BYTES = {
+    "peaks_one": lambda cells, peaks: 2 * cells + 8 * peaks,
     "peaks_count": lambda cells, peaks: 2 * cells,
     "peaks_write": lambda cells, peaks: 2 * cells + 8 * peaks,
 }
@@ -394,10 +396,8 @@ TRAFFIC_KERNELS = {
                        "c4_batch_4096"),
     "vote_rank_event": ("hough::k_vote_rank<2, 10, true, true>", "paper_1310_7556_amd/csrc/k_vote_rank.hip",
                         "c4_batch_4096"),
-    "peaks_count": ("hough::(anonymous namespace)::k_peaks_rows<8, false, false>",
-                    "paper_1310_7556_amd/csrc/k_peaks_rows.hip", "c4_batch_4096"),
-    "peaks_write": ("hough::(anonymous namespace)::k_peaks_rows<8, true, false>",
-                    "paper_1310_7556_amd/csrc/k_peaks_rows.hip", "c4_batch_4096"),
+    "peaks_one": ("hough::k_peaks_one<8, 16, false, 8>", "paper_1310_7556_amd/csrc/k_peaks_one.hip",
+                  "c4_batch_4096"),
 }
 # SQ counters of the counter profiles: two passes of at most 8 SQ counters
 COUNTER_PASSES = (
@@ -656,7 +656,7 @@ def bench_confirmation(H, torch, reps=5, c4_events=512):
                  ms_per_call=round(wall * 1e3, 4), kernel_ms=kt,
                  clusters_ms=round(sum(v for k, v in kt.items() if k.startswith("cluster_") and
                                        k != "cluster_fit") + kt.get("scan_counts", 0.0), 4),
-                 fit_ms=round(kt.get("cluster_fit", 0.0) + kt.get("bucket_layers", 0.0), 4))
+                 fit_ms=round(kt.get("cluster_fit", 0.0) + kt.get("hit_index", 0.0), 4))
         if n_ev is None:
             import oracle
             tab = oracle.Tables(spec)

@@ -51,7 +51,7 @@ void free_all(hough_ctx *c)
                     c->d_tile_off, c->d_cand, c->d_cand_counts, c->d_rz_hist, c->d_redo_list, c->d_gap_info, c->d_gap_list,
                     c->d_scan_part, c->d_scan_off, c->d_dir_tab, c->d_cl_rank, c->d_cl_part,
                     c->d_cl_part_off, c->d_part_cnt, c->d_part_base,
-                    c->d_sec_part, c->d_sec_off};
+                    c->d_sec_part, c->d_sec_off, c->d_peak_state};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
     for (auto &t : c->pending) {
@@ -248,6 +248,7 @@ int hough_create(const hough_grid_spec *spec, const hough_limits *limits, int de
     c->scan_blocks_max = scan_blocks(c->n_peak_tiles);
     // split_parts keeps E * K <= E + kSplitPartsPerCu * n_cu (K <= ceil(4 n_cu / E))
     c->max_parts = uint64_t(E) + uint64_t(kSplitPartsPerCu) * c->n_cu;
+    c->n_peak_state = peaks_one_states(*spec, E);
     const size_t nb = buckets ? (size_t(1) << c->bucket_bits) + 1 : 0;
     const size_t ncand = rz ? size_t(E) * spec->rz_max_candidates : 0;
     const size_t rzh = rz ? size_t(c->n_cu) * kMaxRzWavesPerCu * spec->n_z0 : 0;
@@ -264,6 +265,7 @@ int hough_create(const hough_grid_spec *spec, const hough_limits *limits, int de
               dev_alloc(&c->d_part_cnt, c->max_parts * kSplitBins) &&
               dev_alloc(&c->d_part_base, c->max_parts * kSplitBins) &&
               dev_alloc(&c->d_sec_part, buckets ? (uint64_t(E) + uint64_t(kIndexPartsPerCu) * c->n_cu) * kSectorBins : 0) &&
+              dev_alloc(&c->d_peak_state, 2 * c->n_peak_state) &&
               dev_alloc(&c->d_sec_off, buckets ? size_t(E) * (kSectorBins + 1) : 0) &&
               dev_alloc(&c->d_gap_info, size_t(E) * L) && dev_alloc(&c->d_gap_list, H) &&
               dev_alloc(&c->d_scan_part, c->scan_blocks_max) && dev_alloc(&c->d_scan_off, c->scan_blocks_max + 1) &&
@@ -289,6 +291,7 @@ int hough_create(const hough_grid_spec *spec, const hough_limits *limits, int de
     if (err == hipSuccess && !rk_sorted.empty())
         err = hipMemcpy(c->d_rk_sorted, rk_sorted.data(), rk_sorted.size() * 4, hipMemcpyHostToDevice);
     if (err == hipSuccess) err = hipMemset(c->d_counters, 0, kCounterDwords * 4);
+    if (err == hipSuccess) err = hipMemset(c->d_peak_state, 0, 2 * c->n_peak_state * 8);
     if (err == hipSuccess) err = hipDeviceSynchronize();
     // the static scratch of hough_peaks_noalloc: its address on this device,
     // looked up once per device (a failure is reported by that call)

@@ -100,6 +100,8 @@ struct hough_ctx {
     size_t max_lds_direct = 65536;     // LDS budget of the direct vote's table staging
     size_t max_lds_rank = 65536;       // LDS budget of the rank vote (two workgroups per compute unit)
     uint64_t n_peak_tiles = 0;
+    uint64_t *d_peak_state = nullptr;  // [2][n_peak_state] one-launch peak search: look-back states
+    uint64_t n_peak_state = 0;
     uint32_t *d_cl_rank = nullptr;     // [max_peaks] plateau clusters: cluster index of each root
     uint32_t *d_cl_part = nullptr;     // [cluster blocks] roots per block of the peak list
     uint64_t *d_cl_part_off = nullptr; // [cluster blocks + 1] their exclusive prefix
@@ -148,6 +150,12 @@ uint32_t peak_rows_cells_per_lane(const hough_ctx *c, const uint16_t *acc, uint3
 uint32_t peak_rows_strip(const hough_ctx *c);
 hipError_t launch_peaks_rows_pass(hough_ctx *c, bool write, const uint16_t *acc, uint32_t n_events,
                                   hough_peak *peaks, uint64_t capacity, const PeakScratch &ps, hipStream_t s);
+// One-launch peak search (k_peaks_one.hip): whether it applies, the look-back
+// states a context needs for it, the launch.
+bool peaks_one_usable(const hough_ctx *c, const uint16_t *acc, uint32_t n_events);
+uint64_t peaks_one_states(const hough_grid_spec &g, uint64_t max_events);
+hipError_t launch_peaks_one(hough_ctx *c, const uint16_t *acc, uint32_t n_events, hough_peak *peaks, uint64_t capacity,
+                            uint64_t *event_peak_offsets, hipStream_t s);
 // Split forms (k_bucket.hip, k_rz.hip): a batch of E events is cut into K
 // parts per event when E is small, so that a per-event pass runs on many
 // workgroups; K = 0 when the one-workgroup-per-event form is used.
@@ -214,6 +222,8 @@ uint32_t rz_blocks(const hough_ctx *c);
 constexpr uint32_t kMaxRzWavesPerCu = 16;
 // size of the context's array of work-queue counters (dwords)
 constexpr uint32_t kCounterDwords = 512;
+// the one-launch peak search's counters (zero at create)
+constexpr uint32_t kPeakCounterBase = 384;
 // capacity of the list of records the fast rz kernel leaves to the exact path
 // (past it, the exact-path kernel scans every record for the marks)
 constexpr uint32_t kRedoListCap = 1u << 16;

@@ -580,6 +580,8 @@ hipError_t launch_peaks(hough_ctx *c, const uint16_t *acc, uint32_t n_events, ho
 hipError_t launch_peaks(hough_ctx *c, const uint16_t *acc, uint32_t n_events, hough_peak *peaks,
                         uint64_t capacity, uint64_t *event_peak_offsets, hipStream_t s)
 {
+    if (peaks_one_usable(c, acc, n_events))
+        return launch_peaks_one(c, acc, n_events, peaks, capacity, event_peak_offsets, s);
     return launch_peaks(c, acc, n_events, peaks, capacity, event_peak_offsets, s, ctx_peak_scratch(c), true);
 }
 
