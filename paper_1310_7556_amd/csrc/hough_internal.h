@@ -156,6 +156,9 @@ bool peaks_one_usable(const hough_ctx *c, const uint16_t *acc, uint32_t n_events
 uint64_t peaks_one_states(const hough_grid_spec &g, uint64_t max_events);
 hipError_t launch_peaks_one(hough_ctx *c, const uint16_t *acc, uint32_t n_events, hough_peak *peaks, uint64_t capacity,
                             uint64_t *event_peak_offsets, hipStream_t s);
+bool peaks_count_one_usable(const hough_ctx *c, const uint32_t *counts, uint32_t n_events);
+hipError_t launch_peaks_count_one(hough_ctx *c, const uint32_t *counts, uint32_t n_events, uint2 *peaks,
+                                  uint64_t capacity, uint64_t *event_peak_offsets, hipStream_t s);
 // Split forms (k_bucket.hip, k_rz.hip): a batch of E events is cut into K
 // parts per event when E is small, so that a per-event pass runs on many
 // workgroups; K = 0 when the one-workgroup-per-event form is used.

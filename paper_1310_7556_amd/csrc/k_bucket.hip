@@ -5,17 +5,10 @@
 // candidate cell are found in a few buckets.  Order inside a group is
 // unspecified: votes are OR/count updates and every result is independent of
 // hit order.
+#include "device_hits.h"
 #include "hough_internal.h"
 
 namespace hough {
-
-__device__ __forceinline__ void event_range(const uint64_t *offs, uint32_t e, uint64_t n_hits,
-                                            uint64_t &b, uint64_t &end)
-{
-    b = min(offs[e], n_hits);
-    end = min(offs[e + 1], n_hits);
-    if (end < b) end = b;
-}
 
 // One workgroup per event: layer histogram, prefix, scatter.
 __global__ void __launch_bounds__(1024)
@@ -173,35 +166,6 @@ k_layer_scatter(const uint8_t *__restrict__ layer, const uint32_t *__restrict__ 
         }
         __syncthreads();
     }
-}
-
-// Calls f(layer, phi, index) for every hit of [b, end); with `vec` (layer
-// 4-byte and phi 16-byte aligned) the aligned middle is read four hits per
-// load.
-template <class F>
-__device__ __forceinline__ void indexed_hits(const uint8_t *__restrict__ layer, const uint32_t *__restrict__ phi,
-                                             uint64_t b, uint64_t end, uint32_t t, uint32_t nt, bool vec, F &&f)
-{
-    uint64_t tail = b;
-    if (vec) {
-        const uint64_t a = min((b + 3) & ~uint64_t(3), end);
-        if (t < a - b) f(uint32_t(layer[b + t]), phi[b + t], b + t);
-        const uint64_t nq = (end - a) >> 2;
-        const uint32_t *l4 = reinterpret_cast<const uint32_t *>(layer + a);
-        const uint4 *p4 = reinterpret_cast<const uint4 *>(phi + a);
-#pragma unroll 2
-        for (uint64_t q = t; q < nq; q += nt) {
-            const uint32_t lw = l4[q];
-            const uint4 pw = p4[q];
-            const uint64_t i = a + 4 * q;
-            f(lw & 0xFFu, pw.x, i);
-            f((lw >> 8) & 0xFFu, pw.y, i + 1);
-            f((lw >> 16) & 0xFFu, pw.z, i + 2);
-            f(lw >> 24, pw.w, i + 3);
-        }
-        tail = a + (nq << 2);
-    }
-    for (uint64_t i = tail + t; i < end; i += nt) f(uint32_t(layer[i]), phi[i], i);
 }
 
 // Exclusive prefix of n LDS counters in place, by all NT threads (a multiple

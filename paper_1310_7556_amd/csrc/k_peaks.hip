@@ -593,6 +593,8 @@ hipError_t launch_peaks_count(hough_ctx *c, const uint32_t *counts, uint32_t n_e
     uint32_t rp = std::min(peak_rows(c), c->spec.n_qpt);
     while (rp > 0 && size_t(planes) * (rp + 2) * c->spec.n_phi * 4 > c->max_lds) --rp;
     if (rp == 0) return hipErrorInvalidConfiguration;
+    if (peaks_count_one_usable(c, counts, n_events))
+        return launch_peaks_count_one(c, counts, n_events, peaks, capacity, event_peak_offsets, s);
     const uint32_t n_kt = (c->spec.n_qpt + rp - 1) / rp;
     const uint64_t n_items = uint64_t(n_events) * c->spec.n_d0 * n_kt;
     if (n_events == 0) return launch_scan_counts(c, c->d_tile_counts, 0, c->d_tile_off, 1, event_peak_offsets, s);

@@ -6,19 +6,9 @@
 // A wavefront owns a strip of R consecutive q/pT rows of one event (and one
 // d0 plane): it reads them with a halo row on either side (and, with a d0
 // axis, the same rows of the planes beside it), decides every cell and keeps
-// the decisions as bits.  A workgroup of four strips publishes its count and
-// finds its place by a decoupled look-back over the workgroups before it:
-// wave 0 reads 64 predecessors' states at a time, each {empty, count, or
-// count of everything up to it}, and adds counts until it meets a sum.  Then
-// each row's peaks are compacted in cell order through LDS and stored.
-//
-// The states have to be empty when a launch begins: launches alternate
-// between two arrays (the parity of a launch count kept on the device, so
-// that a replayed graph alternates too), and each clears what the one before
-// it filled.  A workgroup waits only for workgroups of smaller number, and
-// takes its number from a counter when it starts running, so the smallest
-// number still at work never waits and every wait ends.  That counter serves
-// one workgroup per 12 ns, hence eight strips per workgroup on large grids.
+// the decisions as bits.  A workgroup of several strips finds its place by a
+// decoupled look-back over the workgroups before it (look_back.h); then each
+// row's peaks are compacted in cell order through LDS and stored.
 //
 // Bound by HBM on batches (2 bytes per cell read, 8 bytes per peak written),
 // by the chain load, count, look back, store on single events.  Against a
@@ -27,58 +17,10 @@
 // 256 15 -> 8 us, of 1024 x 1024 30 -> 10 us.  Fewer rows per strip cost more
 // numbers: 4096 events with 8 and 4 rows 2164 and 3109 us (16: 1884), all
 // with four strips per workgroup and two counters.
+#include "look_back.h"
 #include "peak_rows.h"
 
 namespace hough {
-
-namespace {
-
-// entries of the counters, each in a cache line of its own
-constexpr uint32_t kNumber = 0, kLaunches = 32, kLastGrid = 33;
-static_assert(kPeakCounterBase + kLastGrid < kCounterDwords, "peak counters fit the counter array");
-
-constexpr uint64_t kStateCount = uint64_t(1) << 62, kStateSum = uint64_t(2) << 62, kStateValue = kStateCount - 1;
-
-__device__ __forceinline__ uint64_t state_load(const uint64_t *p)
-{
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-__device__ __forceinline__ uint32_t load_counter(const uint32_t *p)
-{
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-__device__ __forceinline__ void state_store(uint64_t *p, uint64_t v)
-{
-    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// Sum of the counts of workgroups 0 .. w - 1, by one wave (uniform result).
-__device__ __forceinline__ uint64_t look_back(const uint64_t *state, uint32_t w, uint32_t lane)
-{
-    uint64_t sum = 0;
-    for (int64_t top = int64_t(w) - 1; top >= 0; top -= 64) {
-        const int64_t i = top - int64_t(lane);
-        uint64_t v, sums;
-        for (;;) {
-            v = i >= 0 ? state_load(state + i) : kStateSum;      // before the first: the sum 0
-            sums = __ballot((v & kStateSum) != 0);
-            // the lanes up to the nearest sum have to be filled
-            const uint64_t need = sums ? (sums & (~sums + 1)) - 1 : ~uint64_t(0);
-            if ((__ballot(v == 0) & need) == 0) break;
-            __builtin_amdgcn_s_sleep(1);
-        }
-        const uint32_t last = sums ? uint32_t(__builtin_ctzll(sums)) : 63u;
-        uint64_t x = lane <= last ? v & kStateValue : 0u;
-        for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, 64);
-        sum += x;
-        if (sums) break;
-    }
-    return sum;
-}
-
-}  // namespace
 
 template <int C, int R, bool D3, int WAVES>
 __global__ void __launch_bounds__(64 * WAVES)
@@ -90,21 +32,12 @@ k_peaks_one(const uint16_t *__restrict__ acc, uint32_t n_events, uint32_t n_qpt,
     constexpr int D = C / 2;
     constexpr int kCells = 64 * C;
     __shared__ uint2 rec_s[WAVES][kCells];
-    __shared__ uint32_t wave_cnt[WAVES], number_s, parity_s;
+    __shared__ uint32_t wave_cnt[WAVES], join_s[2];
     __shared__ uint64_t base_s;
     const uint32_t lane = threadIdx.x & 63;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    if (threadIdx.x == 0) {
-        const uint32_t number = atomicAdd(counters + kNumber, 1u);
-        const uint32_t parity = load_counter(counters + kLaunches) & 1u, filled = load_counter(counters + kLastGrid);
-        uint64_t *other = states + (parity ? 0 : n_states);
-        for (uint64_t i = number; i < filled; i += gridDim.x) state_store(other + i, 0);
-        number_s = number;
-        parity_s = parity;
-    }
-    __syncthreads();
-    const uint32_t number = __builtin_amdgcn_readfirstlane(number_s);
-    uint64_t *state = states + (__builtin_amdgcn_readfirstlane(parity_s) ? n_states : 0);
+    uint64_t *state;
+    const uint32_t number = look_back_join(states, n_states, counters, join_s, state);
     const uint64_t tile = uint64_t(number) * WAVES + wave;
     const bool active = tile < n_tiles;
     const uint32_t planes = D3 ? n_d0 : 1u;
@@ -208,19 +141,8 @@ k_peaks_one(const uint16_t *__restrict__ acc, uint32_t n_events, uint32_t n_qpt,
         all += wave_cnt[w];
     }
     if (wave == 0) {
-        if (lane == 0 && number > 0) state_store(state + number, kStateCount | all);
-        const uint64_t sum = look_back(state, number, lane);
-        if (lane == 0) {
-            state_store(state + number, kStateSum | (sum + all));
-            base_s = sum;
-            // the last number's sum means that every workgroup has filled
-            // its state, and so has read the counters
-            if (number == gridDim.x - 1) {
-                counters[kNumber] = 0;
-                counters[kLaunches] += 1;
-                counters[kLastGrid] = gridDim.x;
-            }
-        }
+        const uint64_t sum = look_back_place(state, counters, number, all, lane);
+        if (lane == 0) base_s = sum;
     }
     __syncthreads();
     uint64_t running = base_s + before;
@@ -321,7 +243,192 @@ bool peaks_one_usable(const hough_ctx *c, const uint16_t *acc, uint32_t n_events
 
 uint64_t peaks_one_states(const hough_grid_spec &g, uint64_t max_events)
 {
-    return (max_events * g.n_d0 * ((g.n_qpt + 1) / 2) + 3) / 4;
+    return max_events * g.n_d0 * ((g.n_qpt + 1) / 2);    // the counting form's workgroups, of at least two rows
+}
+
+// Local maxima of a counting accumulator in one launch.  A strip is R
+// consecutive q/pT rows of one event (and d0 plane); a wave takes 256 cells of
+// them, four per lane, and a workgroup one or several whole strips; neighbours across lanes by wave rotates, those of the first
+// and last lane (and across the phi0 wrap) by one more load per row.  The
+// rows' counts per wave give the cell order within the workgroup, the
+// look-back its place.  Bound by the chain load, count, look back, store:
+// 2048 x 2048 cells (16.8 MB): 16 us, where LDS tiles read in three passes took
+// 121 us.
+template <int R, bool D3>
+__global__ void __launch_bounds__(1024)
+k_peaks_count_one(const uint32_t *__restrict__ counts, uint32_t n_events, uint32_t n_qpt, uint32_t n_d0, uint32_t nphi,
+                  uint32_t n_strips, uint64_t n_tiles, uint32_t thr, uint64_t *__restrict__ states, uint64_t n_states,
+                  uint32_t *__restrict__ counters, uint64_t *__restrict__ poff, uint2 *__restrict__ peaks,
+                  uint64_t capacity)
+{
+    __shared__ uint32_t cnt_s[R * 16], pre_s[R * 16], join_s[2];
+    __shared__ uint64_t base_s;
+    const uint32_t lane = threadIdx.x & 63, waves = nphi >> 8, parts = blockDim.x / (nphi >> 2);
+    const uint32_t at = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wave = at % waves, part = at / waves;
+    uint64_t *state;
+    const uint32_t number = look_back_join(states, n_states, counters, join_s, state);
+    const uint32_t planes = D3 ? n_d0 : 1u;
+    const uint64_t tile = min(uint64_t(number) * parts + part, n_tiles - 1);
+    const bool active = uint64_t(number) * parts + part < n_tiles;
+    const uint32_t st = uint32_t(tile % n_strips), dp = uint32_t(tile / n_strips % planes);
+    const uint32_t e = uint32_t(tile / n_strips / planes);
+    const int r0 = int(st) * R;
+    const uint64_t plane = uint64_t(n_qpt) * nphi;
+    const uint32_t *ev = counts + (uint64_t(e) * planes + dp) * plane;
+    const bool has_m = D3 && dp > 0, has_p = D3 && dp + 1 < planes;
+    const uint32_t p0 = wave * 256 + lane * 4;
+    const uint32_t edge = (lane == 63 ? wave * 256 + 256 : wave * 256 + nphi - 1) & (nphi - 1);
+
+    struct Row {
+        uint32_t v[4], x;                            // the lane's cells; the wave's neighbour cell on the lane's side
+    };
+    auto load = [&](const uint32_t *pl, int r) {
+        const uint32_t *row = pl + uint64_t(min(max(r, 0), int(n_qpt) - 1)) * nphi;
+        const uint4 a = *reinterpret_cast<const uint4 *>(row + p0);
+        return Row{{a.x, a.y, a.z, a.w}, row[edge]};
+    };
+    // lr: the larger neighbour in the row; h: that and the cell itself
+    // (everything 0 when the row is absent)
+    auto maxima = [&](Row &w, bool present, uint32_t (&lr)[4], uint32_t (&h)[4]) {
+        const uint32_t keep = present ? 0xFFFFFFFFu : 0u;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) w.v[j] &= keep;
+        w.x &= keep;
+        // the rotates with every lane active, then the choice
+        const uint32_t fl = from_left(w.v[3]), fr = from_right(w.v[0]);
+        const uint32_t l = lane == 0 ? w.x : fl, r = lane == 63 ? w.x : fr;
+        lr[0] = max(l, w.v[1]);
+        lr[1] = max(w.v[0], w.v[2]);
+        lr[2] = max(w.v[1], w.v[3]);
+        lr[3] = max(w.v[2], r);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) h[j] = max(lr[j], w.v[j]);
+    };
+    Row row[R + 2], rowm[D3 ? R + 2 : 1], rowp[D3 ? R + 2 : 1];
+#pragma unroll
+    for (int i = 0; i < R + 2; ++i) {
+        row[i] = load(ev, r0 - 1 + i);
+        if constexpr (D3) {
+            rowm[i] = load(has_m ? ev - plane : ev, r0 - 1 + i);
+            rowp[i] = load(has_p ? ev + plane : ev, r0 - 1 + i);
+        }
+    }
+    auto inside = [&](int i) { return r0 - 1 + i >= 0 && r0 - 1 + i < int(n_qpt); };
+    // strips past the last one have no peaks
+    auto beside = [&](int i, uint32_t (&nb)[4]) {     // the larger h of the neighbour planes' row i
+        uint32_t lr[4], hm[4], hq[4];
+        if constexpr (D3) {
+            maxima(rowm[i], has_m && inside(i), lr, hm);
+            maxima(rowp[i], has_p && inside(i), lr, hq);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) nb[j] = max(hm[j], hq[j]);
+        }
+    };
+    uint32_t bits[R], hp[4], lrc[4], hc[4], nbp[4], nbc[4], lrx[4];
+    maxima(row[0], inside(0), lrx, hp);
+    maxima(row[1], inside(1), lrc, hc);
+    beside(0, nbp);
+    beside(1, nbc);
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+        uint32_t lrn[4], hn[4], nbn[4];
+        maxima(row[i + 2], inside(i + 2), lrn, hn);
+        beside(i + 2, nbn);
+        bits[i] = 0;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            uint32_t mx = max(max(hp[j], hn[j]), lrc[j]);
+            if (D3) mx = max(mx, max(max(nbp[j], nbc[j]), nbn[j]));
+            const uint32_t v = row[i + 1].v[j];
+            bits[i] |= (v >= thr && v >= mx && active && inside(i + 1) ? 1u : 0u) << j;
+            hp[j] = hc[j];
+            hc[j] = hn[j];
+            lrc[j] = lrn[j];
+            nbp[j] = nbc[j];
+            nbc[j] = nbn[j];
+        }
+    }
+    // the lane's place in its wave's part of each row
+    uint32_t place[R];
+    const uint64_t lt = (1ull << lane) - 1ull;
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+        const uint32_t n = uint32_t(__popc(bits[i]));
+        const uint64_t b0 = __ballot(n & 1u), b1 = __ballot(n & 2u), b2 = __ballot(n & 4u);
+        place[i] = uint32_t(__popcll(b0 & lt)) + 2 * uint32_t(__popcll(b1 & lt)) + 4 * uint32_t(__popcll(b2 & lt));
+        if (lane == 0)
+            cnt_s[(part * R + i) * waves + wave] = uint32_t(__popcll(b0)) + 2 * uint32_t(__popcll(b1)) + 4 * uint32_t(__popcll(b2));
+    }
+    __syncthreads();
+    if (at == 0) {
+        const uint32_t n = parts * R * waves;        // at most 64: 16 waves of four rows
+        const uint32_t c = lane < n ? cnt_s[lane] : 0u;
+        uint32_t inc = c;
+        for (uint32_t d = 1; d < 64; d <<= 1) {
+            const uint32_t y = __shfl_up(inc, d, 64);
+            inc += lane >= d ? y : 0u;
+        }
+        if (lane < n) pre_s[lane] = inc - c;
+        const uint32_t all = uint32_t(__builtin_amdgcn_readlane(int(inc), 63));
+        const uint64_t sum = look_back_place(state, counters, number, all, lane);
+        if (lane == 0) {
+            base_s = sum;
+            if (number == gridDim.x - 1) poff[n_events] = sum + all;
+        }
+    }
+    __syncthreads();
+    const uint64_t base = base_s;
+    if (active && st == 0 && dp == 0 && wave == 0 && lane == 0) poff[e] = base + pre_s[part * R * waves];
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+        uint64_t pos = base + pre_s[(part * R + i) * waves + wave] + place[i];
+        const uint32_t cell = (dp * n_qpt + uint32_t(r0 + i)) * nphi + p0;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            if ((bits[i] >> j) & 1u) {
+                if (pos < capacity) peaks[pos] = make_uint2(cell + j, row[i + 1].v[j]);
+                ++pos;
+            }
+        }
+    }
+}
+
+// The default counting peak search for n_phi 256 to 4096.
+bool peaks_count_one_usable(const hough_ctx *c, const uint32_t *counts, uint32_t n_events)
+{
+    const uint32_t n = c->spec.n_phi;
+    return c->tun.peak_rows == 0 && n_events != 0 && c->d_peak_state && n >= 256 && n <= 4096 &&
+           (reinterpret_cast<uintptr_t>(counts) & 15) == 0;
+}
+
+hipError_t launch_peaks_count_one(hough_ctx *c, const uint32_t *counts, uint32_t n_events, uint2 *peaks,
+                                  uint64_t capacity, uint64_t *poff, hipStream_t s)
+{
+    const uint32_t nphi = c->spec.n_phi, n_qpt = c->spec.n_qpt, n_d0 = c->spec.n_d0;
+    // four rows per workgroup, two while that leaves compute units idle
+    const uint64_t four = uint64_t(n_events) * n_d0 * ((n_qpt + 3) / 4);
+    const uint32_t R = four >= uint64_t(c->n_cu) ? 4 : 2;
+    const uint32_t n_strips = (n_qpt + R - 1) / R;
+    const uint64_t n_tiles = uint64_t(n_events) * n_d0 * n_strips;
+    // short rows: several strips per workgroup once there are many (16 waves)
+    const uint32_t parts = n_tiles >= 4 * uint64_t(c->n_cu) ? std::max(1u, 4096 / nphi) : 1u;
+    const uint64_t wgs = (n_tiles + parts - 1) / parts;
+    const uint32_t threads = parts * (nphi / 4);
+    if (wgs > 0xFFFFFFFFull / threads) return hipErrorInvalidConfiguration;
+    KernelTimer t;
+    prof_begin(c, "peaks_count_one", s, &t);
+    auto go = [&](auto rr, auto dd) {
+        hipLaunchKernelGGL((k_peaks_count_one<decltype(rr)::value, decltype(dd)::value>), dim3(uint32_t(wgs)),
+                           dim3(threads), 0, s, counts, n_events, n_qpt, n_d0, nphi, n_strips, n_tiles,
+                           c->spec.threshold, c->d_peak_state, c->n_peak_state, c->d_counters + kPeakCounterBase, poff, peaks, capacity);
+    };
+    using std::integral_constant;
+    if (R == 4 && n_d0 > 1) go(integral_constant<int, 4>{}, std::true_type{});
+    else if (R == 4) go(integral_constant<int, 4>{}, std::false_type{});
+    else if (n_d0 > 1) go(integral_constant<int, 2>{}, std::true_type{});
+    else go(integral_constant<int, 2>{}, std::false_type{});
+    prof_end(c, s, &t);
+    return hipGetLastError();
 }
 
 hipError_t launch_peaks_one(hough_ctx *c, const uint16_t *acc, uint32_t n_events, hough_peak *peaks, uint64_t capacity,

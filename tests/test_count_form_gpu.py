@@ -94,3 +94,63 @@ def test_counts_bound_the_layer_masks(H):
         pop += (m >> b) & 1
     c = H.counts_numpy(cnt).astype(np.int64)
     assert (c >= pop).all() and ((c > 0) == (m > 0)).all()
+
+
+@pytest.mark.parametrize("n_phi", [256, 512, 1024, 4096])
+@pytest.mark.parametrize("n_qpt,n_d0,E", [(1, 1, 1), (5, 1, 3), (35, 3, 2), (130, 1, 40)])
+def test_one_launch_count_peaks_against_the_tile_form(H, n_phi, n_qpt, n_d0, E):
+    # the default one-launch search against the tile form (a row count set by
+    # hand) on random counts with plateaus, ragged strips, d0 planes, one and
+    # several strips per workgroup, thresholds and capacities at the edges
+    import torch
+    E = max(1, E * 512 // n_phi) if E > 3 else E
+    spec = synth.grid_spec("p6_paper_2048_count")
+    spec.update(n_qpt=n_qpt, n_phi=n_phi, n_d0=n_d0, d0_lo_mm=-50.0, d0_hi_mm=50.0)
+    for threshold in (0, 3, 1 << 31):
+        spec["threshold"] = threshold
+        ctx = H.HoughContext(spec, max_events=E, max_hits=1)
+        g = torch.Generator(device="cuda").manual_seed(n_phi + n_qpt)
+        cnt = ctx.new_counts(E)
+        cnt.copy_(torch.randint(0, 5, cnt.shape, generator=g, device="cuda", dtype=torch.int32))
+        cnt[0, 0, 0, :9] = -1                          # 2^32 - 1
+        if n_d0 > 1 and n_phi == 4096:                 # three planes' rows exceed the tile form's LDS: refused
+            with pytest.raises(H.HoughError):
+                ctx.peaks_count(cnt, E)
+            continue
+        got = []
+        for cap in (E * ctx.cells, 7):
+            for tuning in (dict(), dict(peak_rows=2)):
+                ctx.set_tuning(**tuning)
+                pk, off = ctx.new_peaks(cap).fill_(-1), ctx.new_offsets(E).fill_(-1)
+                ctx.peaks_count(cnt, E, capacity=cap, peaks=pk, offsets=off)
+                got.append((pk, off))
+        torch.cuda.synchronize()
+        for a, b in ((got[0], got[1]), (got[2], got[3])):
+            assert torch.equal(a[1], b[1]) and torch.equal(a[0], b[0])
+
+
+@pytest.mark.parametrize("rows", [0, 1, 2, 8, 16, 32])
+@pytest.mark.parametrize("shift", [0, 1])
+def test_count_tiles_of_every_height(H, rows, shift):
+    # ragged last tiles, unaligned hit arrays, unreachable rows, hits of
+    # layers the detector lacks
+    import torch
+    spec = synth.grid_spec("c3_pileup_displaced_3d")
+    spec.update(n_qpt=37, n_phi=256, n_d0=3, d0_lo_mm=-120.0, d0_hi_mm=120.0, threshold=3)
+    batch = ragged()
+    tab = oracle.Tables(spec)
+    assert not tab.V.all()
+    n = batch.n_hits
+    lay = torch.zeros(n + shift, dtype=torch.uint8, device="cuda")[shift:]
+    lay.copy_(torch.from_numpy(batch.layer))
+    phi = torch.zeros(n + shift, dtype=torch.int32, device="cuda")[shift:]
+    phi.copy_(torch.from_numpy(batch.phi.view(np.int32)))
+    ctx = H.HoughContext(spec, max_events=batch.n_events, max_hits=n)
+    if rows:
+        ctx.set_tuning(vote_rows=rows)
+    cnt = ctx.vote_count(H.DeviceHits(lay, phi, None, batch.offsets))
+    torch.cuda.synchronize()
+    got = H.counts_numpy(cnt)
+    for e in range(batch.n_events):
+        ev = batch.event(e)
+        np.testing.assert_array_equal(got[e], oracle.vote_count(tab, ev.layer, ev.phi), err_msg=f"event {e}")
