@@ -51,7 +51,7 @@ void free_all(hough_ctx *c)
                     c->d_tile_off, c->d_cand, c->d_cand_counts, c->d_rz_hist, c->d_redo_list, c->d_gap_info, c->d_gap_list,
                     c->d_scan_part, c->d_scan_off, c->d_dir_tab, c->d_cl_rank, c->d_cl_part,
                     c->d_cl_part_off, c->d_part_cnt, c->d_part_base,
-                    c->d_sec_part, c->d_sec_off, c->d_peak_state};
+                    c->d_sec_part, c->d_sec_off, c->d_peak_state, c->d_row_off, c->d_row_ok};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
     for (auto &t : c->pending) {
@@ -210,6 +210,14 @@ int hough_create(const hough_grid_spec *spec, const hough_limits *limits, int de
     std::vector<uint8_t> V(nOV);
     build_offsets(*spec, O.data(), V.data());
     c->all_valid = std::all_of(V.begin(), V.end(), [](uint8_t v) { return v != 0; });
+    const bool by_row = spec->n_phi >= 64 && uint64_t(c->rows) * spec->n_phi <= kRowsCellsMax;
+    const uint32_t n_by_row = by_row ? c->rows : 0;
+    std::vector<uint32_t> row_off(size_t(n_by_row) * kMaxLayers, 0u), row_ok(n_by_row, 0u);
+    for (uint32_t l = 0; l < spec->n_layers; ++l)
+        for (uint32_t r = 0; r < n_by_row; ++r) {
+            row_off[size_t(r) * kMaxLayers + l] = O[size_t(l) * c->rows + r];
+            row_ok[r] |= V[size_t(l) * c->rows + r] ? 1u << l : 0u;
+        }
     std::vector<int32_t> Z, Zl;
     if (rz) {
         Z.resize(size_t(spec->n_qpt) * spec->n_layers * spec->n_cot);
@@ -265,6 +273,7 @@ int hough_create(const hough_grid_spec *spec, const hough_limits *limits, int de
               dev_alloc(&c->d_part_cnt, c->max_parts * kSplitBins) &&
               dev_alloc(&c->d_part_base, c->max_parts * kSplitBins) &&
               dev_alloc(&c->d_sec_part, buckets ? (uint64_t(E) + uint64_t(kIndexPartsPerCu) * c->n_cu) * kSectorBins : 0) &&
+              (!by_row || (dev_alloc(&c->d_row_off, row_off.size()) && dev_alloc(&c->d_row_ok, row_ok.size()))) &&
               dev_alloc(&c->d_peak_state, 2 * c->n_peak_state) &&
               dev_alloc(&c->d_sec_off, buckets ? size_t(E) * (kSectorBins + 1) : 0) &&
               dev_alloc(&c->d_gap_info, size_t(E) * L) && dev_alloc(&c->d_gap_list, H) &&
@@ -282,6 +291,8 @@ int hough_create(const hough_grid_spec *spec, const hough_limits *limits, int de
     hipError_t err = hipMemset(c->d_O, 0, (nOV + kOPad) * 4);
     if (err == hipSuccess) err = hipMemcpy(c->d_O, O.data(), nOV * 4, hipMemcpyHostToDevice);
     if (err == hipSuccess) err = hipMemcpy(c->d_V, V.data(), nOV, hipMemcpyHostToDevice);
+    if (err == hipSuccess && by_row) err = hipMemcpy(c->d_row_off, row_off.data(), row_off.size() * 4, hipMemcpyHostToDevice);
+    if (err == hipSuccess && by_row) err = hipMemcpy(c->d_row_ok, row_ok.data(), row_ok.size() * 4, hipMemcpyHostToDevice);
     if (err == hipSuccess && rz) err = hipMemcpy(c->d_Z, Z.data(), Z.size() * 4, hipMemcpyHostToDevice);
     if (err == hipSuccess && !Zl.empty())
         err = hipMemcpy(c->d_Zl, Zl.data(), Zl.size() * 4, hipMemcpyHostToDevice);

@@ -42,6 +42,9 @@ struct KernelStat {
 
 }  // namespace hough
 
+// Most cells the row form of the vote is chosen for (rows_vote_default).
+constexpr uint64_t kRowsCellsMax = uint64_t(1) << 22;
+
 struct hough_ctx {
     hough_grid_spec spec{};
     hough_limits lim{};
@@ -59,6 +62,8 @@ struct hough_ctx {
     // tables (device)
     uint32_t *d_O = nullptr;     // [L][rows] + kOPad zero entries
     uint8_t *d_V = nullptr;      // [L][rows]
+    uint32_t *d_row_off = nullptr;   // [rows][16] the offsets by row (0 past n_layers); null above kRowsCellsMax
+    uint32_t *d_row_ok = nullptr;    // [rows] bit l: the row can be reached from layer l
     int32_t *d_Z = nullptr;      // [n_qpt][L][n_cot]
     int32_t *d_Zl = nullptr;     // [n_qpt][n_cot][16] = Z + z0_lo (0 past n_layers), when rz_fast
     bool all_valid = true;       // every (layer, row) reachable
@@ -213,6 +218,9 @@ uint32_t vote_rows(const hough_ctx *c);
 hipError_t launch_vote_gaps(hough_ctx *c, const hough_hits *h, uint16_t *acc, hipStream_t s);
 hipError_t launch_vote_direct(hough_ctx *c, const hough_hits *h, uint16_t *acc, hipStream_t s);
 bool direct_vote_usable(const hough_ctx *c);
+bool bounds_by_layer(const hough_ctx *c, uint32_t n_events);
+bool rows_vote_default(const hough_ctx *c, uint32_t n_events);
+hipError_t launch_vote_rows(hough_ctx *c, const hough_hits *h, uint16_t *acc, hipStream_t s);
 hipError_t launch_vote_bounds(hough_ctx *c, const hough_hits *h, hipStream_t s);
 // rank form: spec support, host tables (built at create), usability, launch
 bool rank_vote_usable(const hough_ctx *c, const uint16_t *acc);

@@ -250,6 +250,9 @@ uint32_t vote_rows(const hough_ctx *c)
 hipError_t launch_vote(hough_ctx *c, const hough_hits *h, uint16_t *acc, hipStream_t s)
 {
     if (h->n_events == 0) return hipSuccess;
+    if (c->tun.vote_algo == 0 && !c->tun.vote_items && !c->tun.vote_rows && !c->tun.vote_threads &&
+        !c->tun.vote_wgs_per_cu && rows_vote_default(c, h->n_events))
+        return launch_vote_rows(c, h, acc, s);
     if ((c->tun.vote_algo == 0 || c->tun.vote_algo == 5) && rank_vote_usable(c, acc))
         return launch_vote_rank(c, h, acc, s);
     if ((c->tun.vote_algo == 0 || c->tun.vote_algo == 4 || c->tun.vote_algo == 5) && direct_vote_usable(c))

@@ -24,6 +24,8 @@
 // masks go straight to HBM.
 #include "hough_internal.h"
 
+#include "device_hits.h"
+
 namespace hough {
 
 namespace {
@@ -128,6 +130,76 @@ k_vote_bounds(const uint8_t *__restrict__ layer, const uint32_t *__restrict__ ph
             out[i] = hi >= lo ? make_uint2(lo, hi - lo) : make_uint2(0xFFFFFFFFu, 0u);
         }
         __syncthreads();
+    }
+}
+
+constexpr uint32_t kBoundsQuads = 4;                 // four-hit loads in flight per thread
+
+// k_vote_bounds for few events, a workgroup per (event, layer): every
+// workgroup walks all of the event's hits and keeps those of its own layer,
+// so the rows are written without a merge and L times as many compute units
+// take part.  Bound by the latency of the hit loads, hence the batches of
+// kBoundsQuads (16 events of 150k hits on 10 x 512 entries: 18.5 us, 30 with
+// one load at a time, 64 in the split form below; one event of 20k hits on 10
+// x 1024: 6.8 us, 12 in one workgroup).
+__global__ void __launch_bounds__(1024)
+k_vote_bounds_layer(const uint8_t *__restrict__ layer, const uint32_t *__restrict__ phi,
+                    const uint64_t *__restrict__ offs, uint64_t n_hits, uint32_t n_layers, uint32_t nphi,
+                    uint32_t shift, int vec, uint2 *__restrict__ tab)
+{
+    HOUGH_DYNAMIC_LDS(uint32_t, lds);                // bmin[nphi], bmax[nphi]
+    const uint32_t e = blockIdx.x / n_layers, own = blockIdx.x % n_layers, t = threadIdx.x, nt = blockDim.x;
+    const uint32_t wmask = (1u << shift) - 1u;
+    uint64_t b, end;
+    event_range(offs, e, n_hits, b, end);
+    uint32_t *bmin = lds, *bmax = lds + nphi;
+    for (uint32_t j = t; j < nphi; j += nt) {
+        bmin[j] = 0xFFFFFFFFu;
+        bmax[j] = 0u;
+    }
+    __syncthreads();
+    auto take = [&](uint32_t l, uint32_t ph) {
+        if (l == own) {
+            atomicMin(&bmin[ph >> shift], ph);
+            atomicMax(&bmax[ph >> shift], ph);
+        }
+    };
+    uint64_t tail = b;
+    if (vec) {
+        const uint64_t a = min((b + 3) & ~uint64_t(3), end);
+        if (t < a - b) take(layer[b + t], phi[b + t]);
+        const uint64_t nq = (end - a) >> 2;
+        const uint32_t *l4 = reinterpret_cast<const uint32_t *>(layer + a);
+        const uint4 *p4 = reinterpret_cast<const uint4 *>(phi + a);
+        for (uint64_t q = t; q < nq; q += kBoundsQuads * nt) {
+            uint32_t lw[kBoundsQuads];
+            uint4 pw[kBoundsQuads];
+#pragma unroll
+            for (uint32_t i = 0; i < kBoundsQuads; ++i) {
+                const uint64_t k = min(q + i * nt, nq - 1);
+                lw[i] = q + i * nt < nq ? l4[k] : 0xFFFFFFFFu;   // layer 255: nobody's own
+                pw[i] = p4[k];
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (uint32_t i = 0; i < kBoundsQuads; ++i) {
+                take(lw[i] & 0xFFu, pw[i].x);
+                take((lw[i] >> 8) & 0xFFu, pw[i].y);
+                take((lw[i] >> 16) & 0xFFu, pw[i].z);
+                take(lw[i] >> 24, pw[i].w);
+            }
+        }
+        tail = a + (nq << 2);
+    }
+    for (uint64_t i = tail + t; i < end; i += nt) take(layer[i], phi[i]);
+    __syncthreads();
+    uint2 *out = tab + size_t(blockIdx.x) * nphi;
+    for (uint32_t j = t; j < nphi; j += nt) {
+        const uint32_t jn = (j + 1) & (nphi - 1);
+        const bool ne = bmin[j] <= bmax[j], ne1 = bmin[jn] <= bmax[jn];
+        const uint32_t lo = ne ? (bmax[j] & wmask) + 1u : 0u;        // may equal W: never empty
+        const uint32_t hi = ne1 ? (bmin[jn] & wmask) : wmask;
+        out[j] = hi >= lo ? make_uint2(lo, hi - lo) : make_uint2(0xFFFFFFFFu, 0u);
     }
 }
 
@@ -350,6 +422,15 @@ bool direct_vote_usable(const hough_ctx *c)
     return c->d_dir_tab != nullptr && size_t(c->spec.n_phi) * 8 <= c->max_lds;
 }
 
+// A workgroup per (event, layer) where two per compute unit hold them all:
+// beyond, reading every hit once per layer costs more than one workgroup per
+// event does (24k hits each, 128 events: 27 us against 13.5; 37 events: 11.2
+// against 11.8).
+bool bounds_by_layer(const hough_ctx *c, uint32_t n_events)
+{
+    return uint64_t(n_events) * c->spec.n_layers <= 2 * uint64_t(c->n_cu);
+}
+
 hipError_t launch_vote_bounds(hough_ctx *c, const hough_hits *h, hipStream_t s)
 {
     const uint32_t E = h->n_events;
@@ -357,13 +438,21 @@ hipError_t launch_vote_bounds(hough_ctx *c, const hough_hits *h, hipStream_t s)
     const int vec = (reinterpret_cast<uintptr_t>(h->layer) & 3) == 0 && (reinterpret_cast<uintptr_t>(h->phi) & 15) == 0;
     KernelTimer t;
     prof_begin(c, "vote_bounds", s, &t);
-    // split only events with many hits per table entry (at least 16): the
-    // split form costs two more launches, and each part initialises and
-    // merges its event's whole (layer, bucket) table (the 198k-hit displaced
-    // event: 42 us in one workgroup, 22 us in 64 parts; the 20k-hit event on
-    // 10 x 1024 entries: 13 us in one, 18 us in 64 parts)
     const uint64_t entries = uint64_t(c->spec.n_layers) * c->spec.n_phi;
     const uint64_t per_event = E ? h->n_hits / E : 0;
+    // by layer, but for a few very large events, whose hits are split (the
+    // split form costs two more launches, and each part initialises and merges
+    // its event's whole table): one event of 210k hits 20.1 us by layer and
+    // 20.2 split, of 300k 27 and 21; four of 300k 28.4 and 28.9; 16 of 300k 32
+    // and 71
+    if (bounds_by_layer(c, E) && (per_event <= (1u << 18) || E >= 8)) {
+        hipLaunchKernelGGL(k_vote_bounds_layer, dim3(E * c->spec.n_layers), dim3(1024), size_t(c->spec.n_phi) * 8, s,
+                           h->layer, h->phi, h->event_offsets, h->n_hits, c->spec.n_layers, c->spec.n_phi, c->shift,
+                           vec, c->d_dir_tab);
+        prof_end(c, s, &t);
+        return hipGetLastError();
+    }
+    // otherwise split events with many hits per table entry (at least 16)
     const uint32_t K = per_event >= 16 * entries ? split_parts(c, E) : 0;
     if (K >= 2) {
         const uint64_t n = uint64_t(E) * entries;
