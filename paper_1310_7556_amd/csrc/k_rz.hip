@@ -832,8 +832,10 @@ k_rz_vote_fast(RzParams P)
 }
 
 // Dense form of the fast kernel, for events whose cells hold many members.
-// One workgroup of four waves per candidate: the member list is gathered
-// once, wave w counts cot bins 64 w .. 64 w + 63 (then + 256), one per lane.
+// One workgroup per candidate: the member list is gathered once; pass w
+// counts cot bins 64 w .. 64 w + 63 (then + 256), one per lane, and two waves
+// share a pass's counters: wave w takes the even layers' members, wave w + 4
+// the odd ones', and each sweeps half of the counter rows.
 //
 // What bounds the one-wave form here: its counters and lists leave four
 // waves per compute unit, a wave walks its four passes one after another,
@@ -841,21 +843,28 @@ k_rz_vote_fast(RzParams P)
 // every vote pays for the running maximum (the atomic's return value, five
 // more instructions).  Here a vote is one atomic without a return value; a
 // pass ends with one sweep over the lane's counters that takes the largest
-// count, two packed maxima per four counters, and clears them; the z0 bin
-// is found for the winning cot bin alone, from a histogram of its votes.
-// Counts are bytes: a pass sweeps (without clearing) before they could pass
-// 255, and a candidate whose count really does is left to k_rz_redo.
-// 16 events of 100 to 10,000 tracks (members 20 to 1100 per cell, 16,384
-// candidates): 733 -> 373 us; one event of 1000 tracks, 1024 candidates: 151
-// -> 26 us.
-constexpr uint32_t kDenseThreads = 256, kDenseWaves = kDenseThreads / 64;
+// count, two packed maxima per four counters, sums and clears them; the z0
+// bin is found for the winning cot bin alone, from a histogram of its votes.
+// Counts are bytes; a count that passed 255 shows in the sum, which is then
+// less than the votes cast (by 255 or 256 each time), and the candidate is
+// left to k_rz_redo.
+//
+// Bound by the chain of a candidate (gather, votes, sweep, histogram, each
+// behind a barrier): the counters of 256 cot bins take 65 KB, so two
+// workgroups per compute unit.  16 events of 100 to 10,000 tracks (members 20
+// to 1100 per cell, 16,384 candidates): one-wave form 733 us; one wave per
+// pass 376 us, two 317, three 332, four 373; one event of 1000 tracks, 1024
+// candidates: 151, 25.7, 23.4, 24.2 and 27.6 us.
+constexpr uint32_t kDenseColumns = 4;         // 64-cot passes counted at once
+constexpr uint32_t kDenseShare = 2;           // waves that vote into one pass's counters
+constexpr uint32_t kDenseWaves = kDenseColumns * kDenseShare, kDenseThreads = kDenseWaves * 64;
 constexpr uint32_t kDenseList = 3072;         // scanned hits a candidate may have
 
 __host__ __device__ inline uint32_t rz_dense_rows(uint32_t n_z0) { return n_z0 / 4 + 1; }
 __host__ __device__ inline size_t rz_dense_lds(uint32_t n_z0)
 {
-    return size_t(kDenseWaves) * rz_dense_rows(n_z0) * 256 + size_t(kDenseList) * 4 +
-           size_t(n_z0) * 4;
+    return size_t(kDenseColumns) * rz_dense_rows(n_z0) * 256 + size_t(kDenseList) * 4 +
+           size_t(n_z0 > 2 * kDenseColumns * 64 ? n_z0 : 2 * kDenseColumns * 64) * 4;
 }
 
 __device__ __forceinline__ uint32_t pk_max16(uint32_t a, uint32_t b)
@@ -898,15 +907,20 @@ __global__ void __launch_bounds__(kDenseThreads) k_rz_vote_dense(RzParams P)
     __shared__ uint32_t wave_cnt[kDenseWaves], wave_cot[kDenseWaves], wave_ovf[kDenseWaves], bin_s;
     const uint32_t t = threadIdx.x, lane = t & 63;
     const uint32_t wave = uni(t >> 6);
+    const uint32_t pass = wave % kDenseColumns, share = wave / kDenseColumns;
     const uint32_t rows = rz_dense_rows(P.n_z0), full = P.n_z0 / 4;
-    uint32_t *col = lds + wave * rows * 64 + lane;            // this lane's counters: row stride 64 dwords
-    int32_t *list = reinterpret_cast<int32_t *>(lds + kDenseWaves * rows * 64);
+    uint32_t *col = lds + pass * rows * 64 + lane;            // this lane's counters: row stride 64 dwords
+    int32_t *list = reinterpret_cast<int32_t *>(lds + kDenseColumns * rows * 64);
+    // zeros between their uses: each cot bin's largest count and votes (to
+    // join the shares), then the winning cot bin's histogram
     uint32_t *hist = reinterpret_cast<uint32_t *>(list + kDenseList);
+    uint32_t *part_max = hist + pass * 64 + lane, *part_sum = part_max + kDenseColumns * 64;
+    const uint32_t sweep0 = full * share / kDenseShare, sweep1 = full * (share + 1) / kDenseShare;
     const uint32_t nl = P.n_layers, nb = 1u << P.bucket_bits, bsh = 32 - P.bucket_bits;
-    const uint32_t bytes_last = P.n_z0 % 4 ? (1u << (8 * (P.n_z0 % 4))) - 1u : 0u;   // real bins of the last row
+    const uint32_t bytes_last = (1u << (8 * (P.n_z0 % 4))) - 1u;    // real bins of the last row, the rest counts trash
     const uint64_t total = min(P.roff[P.n_events], P.out_capacity), step = gridDim.x;
-    for (uint32_t r = 0; r < rows; ++r) col[r * 64] = 0;
-    for (uint32_t i = t; i < P.n_z0; i += kDenseThreads) hist[i] = 0;
+    for (uint32_t r = share; r < rows; r += kDenseShare) col[r * 64] = 0;
+    for (uint32_t i = t; i < max(P.n_z0, 2 * kDenseColumns * 64); i += kDenseThreads) hist[i] = 0;
     auto bin_of = [&](uint32_t u) -> uint32_t {
         if (MUL == 2) return mulhi_u24(P.bm, min(u, P.span24));
         return min(uint32_t(__umulhi(u, P.bm)) >> P.bs, P.n_z0);
@@ -976,7 +990,7 @@ __global__ void __launch_bounds__(kDenseThreads) k_rz_vote_dense(RzParams P)
                 zc[4 * g + 3] = v.w;
             }
         };
-        load_rows(wave * 64 + lane);
+        load_rows(pass * 64 + lane);
 
         const uint32_t len = len1 + len2;
         uint32_t incl = len;
@@ -1038,94 +1052,106 @@ __global__ void __launch_bounds__(kDenseThreads) k_rz_vote_dense(RzParams P)
         uint32_t best_c = 0, best_j = 0;       // uniform over the wave
         bool ovf = !fits;
         if (fits) {
-            for (uint32_t j0 = wave * 64; j0 < P.n_cot; j0 += kDenseThreads) {
-                if (j0 != wave * 64) load_rows(j0 + lane);
-                uint32_t room = 255;                          // votes before a count could pass 255
-                uint32_t m1 = 0, m2 = 0;
-                auto sweep = [&](bool clear) {
-                    uint32_t r0 = 0;
-                    for (; r0 + 8 <= full; r0 += 8) {
+            for (uint32_t jr = 0; jr < P.n_cot; jr += kDenseColumns * 64) {
+                const uint32_t j0 = jr + pass * 64;
+                if (jr) load_rows(j0 + lane);
+                uint32_t votes_cast = 0;
+                if (j0 < P.n_cot) {
+                    uint32_t l = share;
+                    uint32_t n = l < nl ? uni(cnt_s[l]) : 0, at = l < nl ? uni(start_s[l]) : 0;
+                    int32_t znext = lane < n ? list[at + lane] : 0;       // the next layer's first members, read ahead
+                    for (; l < nl; l += kDenseShare) {
+                        const uint32_t nc = n, ac = at;
+                        int32_t z = znext;
+                        if (l + kDenseShare < nl) {
+                            n = uni(cnt_s[l + kDenseShare]);
+                            at = uni(start_s[l + kDenseShare]);
+                            znext = lane < n ? list[at + lane] : 0;
+                        }
+                        const uint32_t zl = zc[l];
+                        // (Z + z0_lo) is monotone in the cot bin: its range over the pass
+                        const int32_t za = __builtin_amdgcn_readlane(int(zl), 0), zb = __builtin_amdgcn_readlane(int(zl), 63);
+                        const int32_t mn = min(za, zb), mx = max(za, zb);
+                        for (uint32_t g0 = 0; g0 < nc; g0 += 64) {
+                            if (g0) z = g0 + lane < nc ? list[ac + g0 + lane] : 0;
+                            const bool act = g0 + lane < nc && z >= mn && (z < mx || uint64_t(uint32_t(z - mx)) < P.span);
+                            uint64_t bal = __ballot(act);
+                            uint32_t nq = uint32_t(__popcll(bal));
+                            votes_cast += nq;
+                            auto votes = [&](auto qc) {
+                                constexpr uint32_t Q = decltype(qc)::value;
+                                uint32_t b[Q];
+#pragma unroll
+                                for (uint32_t q = 0; q < Q; ++q)
+                                    b[q] = bin_of(uint32_t(__builtin_amdgcn_readlane(z, int(take_bit(bal)))) - zl);
+#pragma unroll
+                                for (uint32_t q = 0; q < Q; ++q)
+                                    __hip_atomic_fetch_add(col + (b[q] >> 2) * 64, 1u << ((b[q] << 3) & 31u),
+                                                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                            };
+                            for (; nq >= 4; nq -= 4) votes(std::integral_constant<uint32_t, 4>{});
+                            for (; nq; --nq) votes(std::integral_constant<uint32_t, 1>{});
+                        }
+                    }
+                }
+                __syncthreads();                              // every share's votes
+                // the largest count of this share's rows, cleared; the votes
+                // found less the votes cast
+                uint32_t m1 = 0, m2 = 0, found = 0u - votes_cast;
+                if (j0 < P.n_cot) {
+                    uint32_t r0 = sweep0;
+                    for (; r0 + 8 <= sweep1; r0 += 8) {
                         uint32_t x[8];
 #pragma unroll
                         for (uint32_t i = 0; i < 8; ++i) x[i] = col[(r0 + i) * 64];
-                        if (clear) {
 #pragma unroll
-                            for (uint32_t i = 0; i < 8; ++i) col[(r0 + i) * 64] = 0;
-                        }
+                        for (uint32_t i = 0; i < 8; ++i) col[(r0 + i) * 64] = 0;
 #pragma unroll
                         for (uint32_t i = 0; i < 8; ++i) {
                             m1 = pk_max16(m1, x[i]);                       // the high bytes decide
                             m2 = pk_max16(m2, (x[i] & 0x00FF00FFu));       // the low bytes
+                            found = __builtin_amdgcn_sad_u8(x[i], 0u, found);
                         }
                     }
-                    for (; r0 < full; ++r0) {
+                    for (; r0 < sweep1; ++r0) {
                         const uint32_t x = col[r0 * 64];
-                        if (clear) col[r0 * 64] = 0;
+                        col[r0 * 64] = 0;
                         m1 = pk_max16(m1, x);
                         m2 = pk_max16(m2, x & 0x00FF00FFu);
+                        found = __builtin_amdgcn_sad_u8(x, 0u, found);
                     }
-                    if (bytes_last) {                         // the trash bin shares this row
-                        const uint32_t x = col[full * 64] & bytes_last;
+                    if (share == kDenseShare - 1) {           // the trash bin's row
+                        const uint32_t w = col[full * 64], x = w & bytes_last;
+                        col[full * 64] = 0;
                         m1 = pk_max16(m1, x);
                         m2 = pk_max16(m2, x & 0x00FF00FFu);
+                        found = __builtin_amdgcn_sad_u8(x, 0u, found) + (w >> (8 * (P.n_z0 % 4)));
                     }
-                    if (clear) col[full * 64] = 0;
-                };
-                auto lane_max = [&]() {
-                    const uint32_t hi = max((m1 >> 8) & 0xFFu, m1 >> 24), lo = max(m2 & 0xFFFFu, m2 >> 16);
-                    return max(hi, lo);
-                };
-                uint32_t n = uni(cnt_s[0]), at = uni(start_s[0]);
-                int32_t znext = lane < n ? list[at + lane] : 0;       // the next layer's first members, read ahead
-                for (uint32_t l = 0; l < nl; ++l) {
-                    const uint32_t nc = n, ac = at;
-                    int32_t z = znext;
-                    if (l + 1 < nl) {
-                        n = uni(cnt_s[l + 1]);
-                        at = uni(start_s[l + 1]);
-                        znext = lane < n ? list[at + lane] : 0;
-                    }
-                    const uint32_t zl = zc[l];
-                    // (Z + z0_lo) is monotone in the cot bin: its range over the pass
-                    const int32_t za = __builtin_amdgcn_readlane(int(zl), 0), zb = __builtin_amdgcn_readlane(int(zl), 63);
-                    const int32_t mn = min(za, zb), mx = max(za, zb);
-                    for (uint32_t g0 = 0; g0 < nc; g0 += 64) {
-                        if (g0) z = g0 + lane < nc ? list[ac + g0 + lane] : 0;
-                        const bool act = g0 + lane < nc && z >= mn && (z < mx || uint64_t(uint32_t(z - mx)) < P.span);
-                        uint64_t bal = __ballot(act);
-                        uint32_t nq = uint32_t(__popcll(bal));
-                        if (nq > room) {
-                            sweep(false);
-                            room = 255u - wave_max_u32(lane_max());
-                            if (nq > room) { ovf = true; break; }
-                        }
-                        room -= nq;
-                        auto votes = [&](auto qc) {
-                            constexpr uint32_t Q = decltype(qc)::value;
-                            uint32_t b[Q];
-#pragma unroll
-                            for (uint32_t q = 0; q < Q; ++q)
-                                b[q] = bin_of(uint32_t(__builtin_amdgcn_readlane(z, int(take_bit(bal)))) - zl);
-#pragma unroll
-                            for (uint32_t q = 0; q < Q; ++q)
-                                __hip_atomic_fetch_add(col + (b[q] >> 2) * 64, 1u << ((b[q] << 3) & 31u),
-                                                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                        };
-                        for (; nq >= 4; nq -= 4) votes(std::integral_constant<uint32_t, 4>{});
-                        for (; nq; --nq) votes(std::integral_constant<uint32_t, 1>{});
-                    }
-                    if (ovf) break;
                 }
-                m1 = 0;
-                m2 = 0;
-                sweep(true);
-                const uint32_t mine = j0 + lane < P.n_cot ? lane_max() : 0u;
-                const uint32_t most = wave_max_u32(mine);
-                if (most > best_c) {
-                    best_c = most;
-                    best_j = j0 + uint32_t(__ffsll(static_cast<unsigned long long>(__ballot(mine == most)))) - 1;
+                const uint32_t hi = max((m1 >> 8) & 0xFFu, m1 >> 24), lo = max(m2 & 0xFFFFu, m2 >> 16);
+                uint32_t mine = max(hi, lo);
+                if (kDenseShare > 1) {
+                    if (share) {
+                        __hip_atomic_fetch_max(part_max, mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                        __hip_atomic_fetch_add(part_sum, found, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                    }
+                    __syncthreads();
+                    if (share == 0) {
+                        mine = max(mine, *part_max);
+                        found += *part_sum;
+                        *part_max = 0;
+                        *part_sum = 0;
+                    }
                 }
-                if (ovf) break;
+                if (share == 0) {
+                    mine = j0 + lane < P.n_cot ? mine : 0u;
+                    ovf = ovf || __ballot(found != 0) != 0;
+                    const uint32_t most = wave_max_u32(mine);
+                    if (most > best_c) {
+                        best_c = most;
+                        best_j = j0 + uint32_t(__ffsll(static_cast<unsigned long long>(__ballot(mine == most)))) - 1;
+                    }
+                }
             }
         }
         load_windows(e1, rec1);

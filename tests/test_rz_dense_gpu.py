@@ -36,6 +36,7 @@ def check(H, spec, events):
     ([2400, 1600], dict(n_phi=16, n_qpt=6, n_cot=1, n_z0=1)),
     ([2400, 1600], dict(n_phi=16, n_qpt=6, cot_lo=1.2, cot_hi=-1.2)),      # Z decreasing
     ([4000, 3000], dict(n_phi=4, n_qpt=4, n_cot=64)),                      # passes past 255 votes
+    ([4000, 3000], dict(n_phi=4, n_qpt=4, n_cot=65, n_z0=39)),             # as many out of range, in a row's last byte
     ([9000, 100], dict(n_phi=2, n_qpt=3, n_cot=33)),                       # more scanned hits than the list holds
     ([2400], dict(n_phi=16, n_qpt=6, z0_lo_um=-20_000_000, z0_hi_um=20_000_000)),   # 32-bit multiply-high
 ])
