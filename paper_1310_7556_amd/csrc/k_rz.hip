@@ -832,10 +832,10 @@ k_rz_vote_fast(RzParams P)
 }
 
 // Dense form of the fast kernel, for events whose cells hold many members.
-// One workgroup per candidate: the member list is gathered once; pass w
-// counts cot bins 64 w .. 64 w + 63 (then + 256), one per lane, and two waves
-// share a pass's counters: wave w takes the even layers' members, wave w + 4
-// the odd ones', and each sweeps half of the counter rows.
+// One workgroup per candidate: the member list is gathered once, in any
+// order; pass w counts cot bins 64 w .. 64 w + 63 (then + 256), one per lane,
+// and two waves share a pass's counters: each takes every second member and
+// sweeps half of the counter rows.  Wave 0 also looks up the next candidates.
 //
 // What bounds the one-wave form here: its counters and lists leave four
 // waves per compute unit, a wave walks its four passes one after another,
@@ -847,24 +847,27 @@ k_rz_vote_fast(RzParams P)
 // bin is found for the winning cot bin alone, from a histogram of its votes.
 // Counts are bytes; a count that passed 255 shows in the sum, which is then
 // less than the votes cast (by 255 or 256 each time), and the candidate is
-// left to k_rz_redo.
+// left to k_rz_redo, as is one of more members than the list holds.
 //
 // Bound by the chain of a candidate (gather, votes, sweep, histogram, each
 // behind a barrier): the counters of 256 cot bins take 65 KB, so two
 // workgroups per compute unit.  16 events of 100 to 10,000 tracks (members 20
-// to 1100 per cell, 16,384 candidates): one-wave form 733 us; one wave per
-// pass 376 us, two 317, three 332, four 373; one event of 1000 tracks, 1024
-// candidates: 151, 25.7, 23.4, 24.2 and 27.6 us.
+// to 1100 per cell, 16,384 candidates): one-wave form 733 us; here with one
+// wave per pass 376, with two sharing it 317 (three 332, four 373), with one
+// list for all layers in place of one per layer, whose few members each left
+// the votes four at most in a row, 286, and with the lookups on one wave
+// alone 267.  One event of 1000 tracks, 1024 candidates: 151, 25.7, 23.4,
+// 20.7 and 19.7 us.
 constexpr uint32_t kDenseColumns = 4;         // 64-cot passes counted at once
-constexpr uint32_t kDenseShare = 2;           // waves that vote into one pass's counters
+constexpr uint32_t kDenseShare = 2;           // waves that vote into one pass's counters (the second hands its sums to the first)
 constexpr uint32_t kDenseWaves = kDenseColumns * kDenseShare, kDenseThreads = kDenseWaves * 64;
-constexpr uint32_t kDenseList = 3072;         // scanned hits a candidate may have
+constexpr uint32_t kDenseList = 2560;         // members a candidate may have (a multiple of 4)
 
 __host__ __device__ inline uint32_t rz_dense_rows(uint32_t n_z0) { return n_z0 / 4 + 1; }
 __host__ __device__ inline size_t rz_dense_lds(uint32_t n_z0)
 {
-    return size_t(kDenseColumns) * rz_dense_rows(n_z0) * 256 + size_t(kDenseList) * 4 +
-           size_t(n_z0 > 2 * kDenseColumns * 64 ? n_z0 : 2 * kDenseColumns * 64) * 4;
+    return size_t(kDenseColumns) * rz_dense_rows(n_z0) * 256 + size_t(kDenseList) * 5 +
+           size_t(n_z0 > kDenseColumns * 64 ? n_z0 : kDenseColumns * 64) * 4;
 }
 
 __device__ __forceinline__ uint32_t pk_max16(uint32_t a, uint32_t b)
@@ -874,22 +877,16 @@ __device__ __forceinline__ uint32_t pk_max16(uint32_t a, uint32_t b)
                                                                   __builtin_bit_cast(u16x2, b)));
 }
 
-// The lowest set bit of m, cleared in m.
-__device__ __forceinline__ uint32_t take_bit(uint64_t &m)
-{
-    const uint32_t i = uint32_t(__builtin_ctzll(m));
-#if defined(__HIP_DEVICE_COMPILE__)
-    asm("s_bitset0_b64 %0, %1" : "+s"(m) : "s"(i));
-#else
-    m &= m - 1;
-#endif
-    return i;
-}
-
 // One layer's window of scanned hits: hit = scan index + (scan index < split
 // ? add1 : add2) relative to the event, and the layer's offset at the row.
 struct RzWindow {
     uint32_t add1, add2, split, o;
+};
+
+// A candidate's event base, cell and scanned hits.
+struct RzDenseCell {
+    uint64_t base;
+    uint32_t cell, scanned;
 };
 
 // MUL as in k_rz_vote_fast: 2 = 24-bit multiply-high, else 32-bit and shift.
@@ -902,28 +899,44 @@ __global__ void __launch_bounds__(kDenseThreads) k_rz_vote_dense(RzParams P)
 {
     HOUGH_DYNAMIC_LDS(uint4, lds4);
     uint32_t *lds = reinterpret_cast<uint32_t *>(lds4);
-    __shared__ RzWindow win_s[kMaxLayers];
-    __shared__ uint32_t cnt_s[kMaxLayers], start_s[kMaxLayers];
-    __shared__ uint32_t wave_cnt[kDenseWaves], wave_cot[kDenseWaves], wave_ovf[kDenseWaves], bin_s;
+    // by the candidate's parity: its windows, the scan index at which each
+    // starts, its cell and event, its members and winning z0 bin
+    __shared__ RzWindow win_s[2][kMaxLayers];
+    __shared__ uint32_t start_s[2][kMaxLayers], members_s[2], bin_s[2];
+    __shared__ RzDenseCell cell_s[2];
+    __shared__ alignas(16) uint32_t pass_z[kDenseColumns][kMaxLayers];       // Z + z0_lo at the pass's best cot bin
+    __shared__ uint32_t pass_cnt[kDenseColumns], pass_cot[kDenseColumns], pass_ovf[kDenseColumns];
     const uint32_t t = threadIdx.x, lane = t & 63;
     const uint32_t wave = uni(t >> 6);
     const uint32_t pass = wave % kDenseColumns, share = wave / kDenseColumns;
     const uint32_t rows = rz_dense_rows(P.n_z0), full = P.n_z0 / 4;
     uint32_t *col = lds + pass * rows * 64 + lane;            // this lane's counters: row stride 64 dwords
     int32_t *list = reinterpret_cast<int32_t *>(lds + kDenseColumns * rows * 64);
-    // zeros between their uses: each cot bin's largest count and votes (to
-    // join the shares), then the winning cot bin's histogram
-    uint32_t *hist = reinterpret_cast<uint32_t *>(list + kDenseList);
-    uint32_t *part_max = hist + pass * 64 + lane, *part_sum = part_max + kDenseColumns * 64;
+    uint8_t *list_l = reinterpret_cast<uint8_t *>(list + kDenseList);
+    // zeros between their uses: each cot bin's largest count and votes found
+    // in the second share's rows, then the winning cot bin's histogram
+    uint32_t *hist = reinterpret_cast<uint32_t *>(list_l + kDenseList);
+    uint32_t *part = hist + pass * 64 + lane;
     const uint32_t sweep0 = full * share / kDenseShare, sweep1 = full * (share + 1) / kDenseShare;
     const uint32_t nl = P.n_layers, nb = 1u << P.bucket_bits, bsh = 32 - P.bucket_bits;
     const uint32_t bytes_last = (1u << (8 * (P.n_z0 % 4))) - 1u;    // real bins of the last row, the rest counts trash
     const uint64_t total = min(P.roff[P.n_events], P.out_capacity), step = gridDim.x;
     for (uint32_t r = share; r < rows; r += kDenseShare) col[r * 64] = 0;
-    for (uint32_t i = t; i < max(P.n_z0, 2 * kDenseColumns * 64); i += kDenseThreads) hist[i] = 0;
+    for (uint32_t i = t; i < max(P.n_z0, kDenseColumns * 64); i += kDenseThreads) hist[i] = 0;
     auto bin_of = [&](uint32_t u) -> uint32_t {
         if (MUL == 2) return mulhi_u24(P.bm, min(u, P.span24));
         return min(uint32_t(__umulhi(u, P.bm)) >> P.bs, P.n_z0);
+    };
+    // this lane's counter of bin b: a bit-field extract and a shift-add
+    const uint32_t colb = uint32_t(reinterpret_cast<uintptr_t>((lds_u32 *)(col)));
+    auto counter_at = [&](uint32_t b) {
+        uint32_t a;
+#if defined(__HIP_DEVICE_COMPILE__)
+        asm("v_bfe_u32 %0, %1, 2, 30\n\tv_lshl_add_u32 %0, %0, 8, %2" : "=&v"(a) : "v"(b), "v"(colb));
+#else
+        a = colb + ((b >> 2) << 8);
+#endif
+        return reinterpret_cast<lds_u32 *>(uintptr_t(a));
     };
     // the four links; indices past the last candidate stay on the last one
     auto event_of = [&](uint64_t c, uint32_t e) {
@@ -964,18 +977,50 @@ __global__ void __launch_bounds__(kDenseThreads) k_rz_vote_dense(RzParams P)
     };
     if (blockIdx.x >= total) return;
     auto clamped = [&](uint64_t c) { return min(c, total - 1); };
+    // wave 0: the windows in its registers, of a candidate (event e, record
+    // rec), to half x of the tables
+    auto place = [&](uint32_t x, uint32_t e, uint2 rec) {
+        const uint32_t len = len1 + len2;
+        uint32_t incl = len;
+        incl += uint32_t(__builtin_amdgcn_update_dpp(0, int(incl), 0x111, 0xF, 0xF, false));   // row_shr:1
+        incl += uint32_t(__builtin_amdgcn_update_dpp(0, int(incl), 0x112, 0xF, 0xF, false));   // row_shr:2
+        incl += uint32_t(__builtin_amdgcn_update_dpp(0, int(incl), 0x114, 0xF, 0xF, false));   // row_shr:4
+        incl += uint32_t(__builtin_amdgcn_update_dpp(0, int(incl), 0x118, 0xF, 0xF, false));   // row_shr:8
+        const uint32_t T = uint32_t(__builtin_amdgcn_readlane(int(incl), 15));
+        if (lane < kMaxLayers) {
+            const uint32_t at = incl - len;
+            start_s[x][lane] = at;
+            win_s[x][lane] = RzWindow{hs1 - at, hs2 - at - len1, at + len1, o};
+        }
+        if (lane == 0) {
+            cell_s[x] = RzDenseCell{uint64_t(min(P.offs[e], P.n_hits)), rec.x, T};
+            members_s[x] = 0;
+            bin_s[x] = 0xFFFFFFFFu;
+        }
+    };
     uint64_t c = blockIdx.x;
-    uint32_t e0 = event_of(c, 0), pk0 = index_of(c, e0);
-    uint2 rec0 = record_of(e0, pk0);
-    load_row(rec0);
-    load_windows(e0, rec0);
-    uint32_t e1 = event_of(clamped(c + step), e0), pk1 = index_of(clamped(c + step), e1);
-    uint2 rec1 = record_of(e1, pk1);
-    uint32_t e2 = event_of(clamped(c + 2 * step), e1), pk2 = index_of(clamped(c + 2 * step), e2);
-    for (; c < total; c += step) {
-        const uint32_t cell = uni(rec0.x), pk = uni(pk0);
+    uint32_t pk0 = 0, e1 = 0, pk1 = 0, e2 = 0, pk2 = 0;
+    uint2 rec1 = make_uint2(0u, 0u);
+    if (wave == 0) {
+        const uint32_t e0 = event_of(c, 0);
+        pk0 = index_of(c, e0);
+        const uint2 rec0 = record_of(e0, pk0);
+        load_row(rec0);
+        load_windows(e0, rec0);
+        place(0, e0, rec0);
+        e1 = event_of(clamped(c + step), e0);
+        pk1 = index_of(clamped(c + step), e1);
+        rec1 = record_of(e1, pk1);
+        load_row(rec1);
+        load_windows(e1, rec1);
+        e2 = event_of(clamped(c + 2 * step), e1);
+        pk2 = index_of(clamped(c + 2 * step), e2);
+    }
+    __syncthreads();
+    for (uint32_t half = 0; c < total; c += step, half ^= 1) {
+        const uint32_t cell = uni(cell_s[half].cell), T = uni(cell_s[half].scanned);
+        const uint64_t eb = uni64(cell_s[half].base);
         const uint32_t k = (cell >> P.log2phi) % P.n_qpt, p = cell & (P.nphi - 1);
-        const uint64_t eb = uni64(min(P.offs[e0], P.n_hits));
         // this lane's first cot bin's (Z + z0_lo) of every layer, as in the fast kernel
         const int32_t *zrow = P.Zl + size_t(k) * P.n_cot * kMaxLayers;
         uint32_t zc[kMaxLayers];
@@ -991,43 +1036,30 @@ __global__ void __launch_bounds__(kDenseThreads) k_rz_vote_dense(RzParams P)
             }
         };
         load_rows(pass * 64 + lane);
+        // lane l: layer l's value at the pass's first cot bin, lane 16 + l at its last
+        auto boundary = [&](uint32_t j0) {
+            return zrow[size_t(min(j0 + ((lane >> 4) & 1u) * 63u, P.n_cot - 1)) * kMaxLayers + (lane & 15u)];
+        };
+        int32_t ends = boundary(pass * 64);
 
-        const uint32_t len = len1 + len2;
-        uint32_t incl = len;
-        incl += uint32_t(__builtin_amdgcn_update_dpp(0, int(incl), 0x111, 0xF, 0xF, false));   // row_shr:1
-        incl += uint32_t(__builtin_amdgcn_update_dpp(0, int(incl), 0x112, 0xF, 0xF, false));   // row_shr:2
-        incl += uint32_t(__builtin_amdgcn_update_dpp(0, int(incl), 0x114, 0xF, 0xF, false));   // row_shr:4
-        incl += uint32_t(__builtin_amdgcn_update_dpp(0, int(incl), 0x118, 0xF, 0xF, false));   // row_shr:8
-        const uint32_t T = uint32_t(__builtin_amdgcn_readlane(int(incl), 15));
-        const bool fits = T <= kDenseList;
-        if (t < kMaxLayers) {
-            const uint32_t at = incl - len;
-            start_s[t] = at;
-            win_s[t] = RzWindow{hs1 - at, hs2 - at - len1, at + len1, o};
-            cnt_s[t] = 0;
-        }
-        if (t == 0) bin_s = 0xFFFFFFFFu;
-        __syncthreads();
-        // the scanned hits over the workgroup; a layer's members are packed
-        // from its window's place in the list, in any order (past the list's
-        // size they are counted)
-        constexpr uint32_t kU = 4;
-        for (uint32_t g0 = t; g0 < T; g0 += kU * kDenseThreads) {
+        // the scanned hits over the workgroup, the members packed into the
+        // list in any order (past the list's size they are counted)
+        constexpr uint32_t kU = 2;
+        for (uint32_t g0 = wave * 64; g0 < T; g0 += kU * kDenseThreads) {
             uint32_t ph[kU], ls[kU], oo[kU];
             int32_t zv[kU];
 #pragma unroll
             for (uint32_t u = 0; u < kU; ++u) {
-                const uint32_t gi = g0 + u * kDenseThreads;
+                const uint32_t gi = g0 + u * kDenseThreads + lane;
                 ls[u] = kMaxLayers;
                 ph[u] = oo[u] = 0;
                 zv[u] = 0;
                 if (gi < T) {
                     uint32_t l = 0;
 #pragma unroll
-                    for (uint32_t d = 8; d > 0; d >>= 1) l += start_s[l + d] <= gi ? d : 0u;
-                    const RzWindow w = win_s[l];
-                    const uint64_t h = eb + (gi + (gi < w.split ? w.add1 : w.add2));
-                    const uint2 ht = P.hit[h];
+                    for (uint32_t d = 8; d > 0; d >>= 1) l += start_s[half][l + d] <= gi ? d : 0u;
+                    const RzWindow w = win_s[half][l];
+                    const uint2 ht = P.hit[eb + (gi + (gi < w.split ? w.add1 : w.add2))];
                     ph[u] = ht.x;
                     zv[u] = int32_t(ht.y);
                     oo[u] = w.o;
@@ -1036,62 +1068,84 @@ __global__ void __launch_bounds__(kDenseThreads) k_rz_vote_dense(RzParams P)
             }
 #pragma unroll
             for (uint32_t u = 0; u < kU; ++u) {
-                if (ls[u] < kMaxLayers && ((ph[u] - oo[u]) >> P.shift) == p) {
-                    const uint32_t pos = atomicAdd(&cnt_s[ls[u]], 1u);
-                    if (fits) list[start_s[ls[u]] + pos] = zv[u];
+                const bool is_m = ls[u] < kMaxLayers && ((ph[u] - oo[u]) >> P.shift) == p;
+                const uint64_t bal = __ballot(is_m);
+                if (bal == 0) continue;              // uniform
+                uint32_t at = 0;
+                if (lane == 0) at = atomicAdd(&members_s[half], uint32_t(__popcll(bal)));
+                at = uni(at) + uint32_t(__popcll(bal & ((1ull << lane) - 1ull)));
+                if (is_m && at < kDenseList) {
+                    list[at] = zv[u];
+                    list_l[at] = uint8_t(ls[u]);
                 }
             }
         }
         __syncthreads();
-        // ahead: the next candidate's row, the record of the one after it
-        // and the index of the one after that
-        load_row(rec1);
-        const uint2 rec2 = record_of(e2, pk2);
-        const uint32_t e3 = event_of(clamped(c + 3 * step), e2), pk3 = index_of(clamped(c + 3 * step), e3);
+        const uint32_t nm = uni(members_s[half]);
+        const bool fits = nm <= kDenseList;
+        // ahead: the next candidate's tables, the row of the one after it, the
+        // record of the one after that and the index of the next
+        uint2 rec2 = make_uint2(0u, 0u);
+        uint32_t e3 = 0, pk3 = 0;
+        if (wave == 0) {
+            place(half ^ 1, e1, rec1);
+            rec2 = record_of(e2, pk2);
+            load_row(rec2);
+            e3 = event_of(clamped(c + 3 * step), e2);
+            pk3 = index_of(clamped(c + 3 * step), e3);
+        }
 
         uint32_t best_c = 0, best_j = 0;       // uniform over the wave
         bool ovf = !fits;
         if (fits) {
             for (uint32_t jr = 0; jr < P.n_cot; jr += kDenseColumns * 64) {
                 const uint32_t j0 = jr + pass * 64;
-                if (jr) load_rows(j0 + lane);
+                if (jr) {
+                    load_rows(j0 + lane);
+                    ends = boundary(j0);
+                }
                 uint32_t votes_cast = 0;
                 if (j0 < P.n_cot) {
-                    uint32_t l = share;
-                    uint32_t n = l < nl ? uni(cnt_s[l]) : 0, at = l < nl ? uni(start_s[l]) : 0;
-                    int32_t znext = lane < n ? list[at + lane] : 0;       // the next layer's first members, read ahead
-                    for (; l < nl; l += kDenseShare) {
-                        const uint32_t nc = n, ac = at;
-                        int32_t z = znext;
-                        if (l + kDenseShare < nl) {
-                            n = uni(cnt_s[l + kDenseShare]);
-                            at = uni(start_s[l + kDenseShare]);
-                            znext = lane < n ? list[at + lane] : 0;
-                        }
-                        const uint32_t zl = zc[l];
-                        // (Z + z0_lo) is monotone in the cot bin: its range over the pass
-                        const int32_t za = __builtin_amdgcn_readlane(int(zl), 0), zb = __builtin_amdgcn_readlane(int(zl), 63);
+                    // this share's members, a lane each: those that can vote
+                    // in range somewhere in the pass ((Z + z0_lo) is monotone
+                    // in the cot bin) vote one after another
+                    for (uint32_t g0 = share; g0 < nm; g0 += 64 * kDenseShare) {
+                        const uint32_t i = g0 + lane * kDenseShare;
+                        const int32_t z = i < nm ? list[i] : 0;
+                        const int32_t l = i < nm ? list_l[i] : 0;
+                        const int32_t za = __shfl(ends, l, 64), zb = __shfl(ends, 16 + l, 64);
                         const int32_t mn = min(za, zb), mx = max(za, zb);
-                        for (uint32_t g0 = 0; g0 < nc; g0 += 64) {
-                            if (g0) z = g0 + lane < nc ? list[ac + g0 + lane] : 0;
-                            const bool act = g0 + lane < nc && z >= mn && (z < mx || uint64_t(uint32_t(z - mx)) < P.span);
-                            uint64_t bal = __ballot(act);
-                            uint32_t nq = uint32_t(__popcll(bal));
-                            votes_cast += nq;
-                            auto votes = [&](auto qc) {
-                                constexpr uint32_t Q = decltype(qc)::value;
-                                uint32_t b[Q];
+                        const bool act = i < nm && z >= mn && (z < mx || uint64_t(uint32_t(z - mx)) < P.span);
+                        const uint64_t bal = __ballot(act);
+                        const uint32_t nq = uint32_t(__popcll(bal));
+                        votes_cast += nq;
+                        // the active ones to lanes 0 .. nq - 1
+                        const uint32_t rank = __builtin_amdgcn_mbcnt_hi(uint32_t(bal >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(bal), 0u));
+                        const int to = int(4 * (act ? rank : nq + lane - rank));
+                        const int zq = __builtin_amdgcn_ds_permute(to, z), lq = __builtin_amdgcn_ds_permute(to, l);
+                        auto votes = [&](auto qc, uint32_t m) {
+                            constexpr uint32_t Q = decltype(qc)::value;
+                            uint32_t b[Q];
 #pragma unroll
-                                for (uint32_t q = 0; q < Q; ++q)
-                                    b[q] = bin_of(uint32_t(__builtin_amdgcn_readlane(z, int(take_bit(bal)))) - zl);
+                            for (uint32_t q = 0; q < Q; ++q)
+                                b[q] = bin_of(uint32_t(__builtin_amdgcn_readlane(zq, int(m + q))) -
+                                              zc[uint32_t(__builtin_amdgcn_readlane(lq, int(m + q)))]);
 #pragma unroll
-                                for (uint32_t q = 0; q < Q; ++q)
-                                    __hip_atomic_fetch_add(col + (b[q] >> 2) * 64, 1u << ((b[q] << 3) & 31u),
-                                                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                            };
-                            for (; nq >= 4; nq -= 4) votes(std::integral_constant<uint32_t, 4>{});
-                            for (; nq; --nq) votes(std::integral_constant<uint32_t, 1>{});
+                            for (uint32_t q = 0; q < Q; ++q)
+                                __hip_atomic_fetch_add(counter_at(b[q]), 1u << ((b[q] << 3) & 31u),
+                                                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                        };
+                        uint32_t m = 0;
+                        for (; m + 8 <= nq; m += 8) votes(std::integral_constant<uint32_t, 8>{}, m);
+                        if (m + 4 <= nq) {
+                            votes(std::integral_constant<uint32_t, 4>{}, m);
+                            m += 4;
                         }
+                        if (m + 2 <= nq) {
+                            votes(std::integral_constant<uint32_t, 2>{}, m);
+                            m += 2;
+                        }
+                        if (m < nq) votes(std::integral_constant<uint32_t, 1>{}, m);
                     }
                 }
                 __syncthreads();                              // every share's votes
@@ -1130,82 +1184,73 @@ __global__ void __launch_bounds__(kDenseThreads) k_rz_vote_dense(RzParams P)
                 }
                 const uint32_t hi = max((m1 >> 8) & 0xFFu, m1 >> 24), lo = max(m2 & 0xFFFFu, m2 >> 16);
                 uint32_t mine = max(hi, lo);
-                if (kDenseShare > 1) {
-                    if (share) {
-                        __hip_atomic_fetch_max(part_max, mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                        __hip_atomic_fetch_add(part_sum, found, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                    }
-                    __syncthreads();
-                    if (share == 0) {
-                        mine = max(mine, *part_max);
-                        found += *part_sum;
-                        *part_max = 0;
-                        *part_sum = 0;
-                    }
-                }
+                if (share) *part = (found << 8) | mine;       // (a difference is small: 24 bits show it)
+                __syncthreads();
                 if (share == 0) {
-                    mine = j0 + lane < P.n_cot ? mine : 0u;
-                    ovf = ovf || __ballot(found != 0) != 0;
+                    const uint32_t other = *part;
+                    *part = 0;
+                    mine = j0 + lane < P.n_cot ? max(mine, other & 0xFFu) : 0u;
+                    ovf = ovf || __ballot(((found << 8) + (other & ~0xFFu)) != 0) != 0;
                     const uint32_t most = wave_max_u32(mine);
                     if (most > best_c) {
                         best_c = most;
-                        best_j = j0 + uint32_t(__ffsll(static_cast<unsigned long long>(__ballot(mine == most)))) - 1;
+                        const uint32_t first = uint32_t(__ffsll(static_cast<unsigned long long>(__ballot(mine == most)))) - 1;
+                        best_j = j0 + first;
+                        if (lane == first) {
+                            uint4 *zs = reinterpret_cast<uint4 *>(pass_z[pass]);
+#pragma unroll
+                            for (uint32_t g = 0; g < kMaxLayers / 4; ++g)
+                                zs[g] = make_uint4(zc[4 * g], zc[4 * g + 1], zc[4 * g + 2], zc[4 * g + 3]);
+                        }
                     }
                 }
             }
         }
-        load_windows(e1, rec1);
-        if (lane == 0) {
-            wave_cnt[wave] = best_c;
-            wave_cot[wave] = best_j;
-            wave_ovf[wave] = ovf;
+        if (wave == 0) load_windows(e2, rec2);
+        if (share == 0 && lane == 0) {
+            pass_cnt[pass] = best_c;
+            pass_cot[pass] = best_j;
+            pass_ovf[pass] = ovf;
         }
         __syncthreads();
-        uint32_t nm = 0, any_ovf = 0;
+        uint32_t any_ovf = 0, best_p = 0;
         best_c = 0;
         best_j = 0xFFFFFFFFu;
-        for (uint32_t l = 0; l < nl; ++l) nm += cnt_s[l];
-        for (uint32_t w = 0; w < kDenseWaves; ++w) {
-            const uint32_t x = wave_cnt[w], j = wave_cot[w];
-            any_ovf |= wave_ovf[w];
+        for (uint32_t w = 0; w < kDenseColumns; ++w) {
+            const uint32_t x = pass_cnt[w], j = pass_cot[w];
+            any_ovf |= pass_ovf[w];
             if (x > best_c || (x == best_c && j < best_j)) {
                 best_c = x;
                 best_j = j;
+                best_p = w;
             }
         }
         if (best_c == 0) best_j = 0;
         if (!any_ovf && best_c != 0) {         // uniform over the workgroup
             // the votes of cot bin best_j: its smallest bin with best_c of them
-            for (uint32_t l = wave; l < nl; l += kDenseWaves) {
-                const uint32_t n = cnt_s[l], at = start_s[l];
-                const uint32_t zl = uint32_t(zrow[size_t(best_j) * kMaxLayers + l]);
-                for (uint32_t i = lane; i < n; i += 64) {
-                    const uint32_t b = bin_of(uint32_t(list[at + i]) - zl);
-                    if (b < P.n_z0) atomicAdd(&hist[b], 1u);
-                }
+            for (uint32_t i = t; i < nm; i += kDenseThreads) {
+                const uint32_t b = bin_of(uint32_t(list[i]) - pass_z[best_p][list_l[i]]);
+                if (b < P.n_z0) atomicAdd(&hist[b], 1u);
             }
             __syncthreads();
             for (uint32_t b = t; b < P.n_z0; b += kDenseThreads) {
-                if (hist[b] == best_c) atomicMin(&bin_s, b);
+                if (hist[b] == best_c) atomicMin(&bin_s[half], b);
                 hist[b] = 0;
             }
             __syncthreads();
         }
         if (t == 0) {
             if (any_ovf) {
-                P.out4[2 * c] = make_uint2(pk, 0u);
+                P.out4[2 * c] = make_uint2(pk0, 0u);
                 P.out4[2 * c + 1] = make_uint2(kRzRedo, nm);
                 const uint32_t i = atomicAdd(P.redo_count, 1u);
                 if (i < P.redo_cap) P.redo_list[i] = c;
             } else {
-                P.out4[2 * c] = make_uint2(pk, best_c ? best_j | (bin_s << 16) : 0u);
+                P.out4[2 * c] = make_uint2(pk0, best_c ? best_j | (bin_s[half] << 16) : 0u);
                 P.out4[2 * c + 1] = make_uint2(best_c, nm);
             }
         }
-        __syncthreads();                       // the list, the counts and bin_s are reused
-        e0 = e1;
         pk0 = pk1;
-        rec0 = rec1;
         e1 = e2;
         pk1 = pk2;
         rec1 = rec2;
