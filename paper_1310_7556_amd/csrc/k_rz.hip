@@ -831,7 +831,8 @@ k_rz_vote_fast(RzParams P)
     }
 }
 
-// Dense form of the fast kernel, for events whose cells hold many members.
+// Dense form of the fast kernel, for cells of many members and for short
+// candidate lists.
 // One workgroup per candidate: the member list is gathered once, in any
 // order; pass w counts cot bins 64 w .. 64 w + 63 (then + 256), one per lane,
 // and two waves share a pass's counters: each takes every second member and
@@ -862,6 +863,8 @@ constexpr uint32_t kDenseColumns = 4;         // 64-cot passes counted at once
 constexpr uint32_t kDenseShare = 2;           // waves that vote into one pass's counters (the second hands its sums to the first)
 constexpr uint32_t kDenseWaves = kDenseColumns * kDenseShare, kDenseThreads = kDenseWaves * 64;
 constexpr uint32_t kDenseList = 2560;         // members a candidate may have (a multiple of 4)
+
+constexpr size_t kDenseStaticLds = 1024;      // at most, beside rz_dense_lds
 
 __host__ __device__ inline uint32_t rz_dense_rows(uint32_t n_z0) { return n_z0 / 4 + 1; }
 __host__ __device__ inline size_t rz_dense_lds(uint32_t n_z0)
@@ -1678,14 +1681,25 @@ hipError_t launch_rz(hough_ctx *c, const hough_hits *h, const hough_peak *peaks,
         while (mcap > 256 && size_t(rz_fast_lds_dwords(hw, mcap)) * 4 > c->max_lds) mcap >>= 1;
     }
     const size_t fast_lds = size_t(rz_fast_lds_dwords(hw, mcap)) * 4;
-    // Cells of many members go to the dense form: from 48 members per cell
-    // on.  Its list is by scanned hits, so it wants the azimuth
-    // buckets narrower than a cell (n_phi <= 2048), and two workgroups per
-    // compute unit.  Any rz knob set by hand keeps the one-wave form.
+    // Cells of many members and short candidate lists go to the dense form:
+    // from 64 members per cell on, where its byte counters and list cost less
+    // than the one-wave form's 8-bit counters (251,000 candidates of 53
+    // members 2730 us against 2359, 131,000 of 76 1512 against 1604, 16,384
+    // of 117 230 against 337; with a single pass of 64 cot bins 194 against
+    // 186), and up to 32 candidates per compute unit,
+    // which the one-wave form spreads over too few waves, eight per ticket
+    // (12 to 47 members, 256 x 256 bins: 1024 candidates 19 to 22 us against
+    // 95 to 120, 4096 57 to 62 against 108 to 131, 8192 101 to 107 against
+    // 121 to 144, 16,384 184 to 195 against 130 to 159).  It scans whole
+    // azimuth buckets, so it wants them narrower than a cell (n_phi <=
+    // 2048), and two workgroups per compute unit.  Any rz knob set by hand
+    // keeps the one-wave form.
     const size_t dense_lds = rz_dense_lds(g.n_z0);
     const bool dense = c->rz_fast && !c->tun.rz_slow_path && !c->tun.rz_counter_bits && !c->tun.rz_waves_per_cu &&
-                       !c->tun.rz_member_cap && per_cell >= 48.0 && c->bucket_bits > c->log2_phi &&
-                       dense_lds + 512 <= c->max_lds_rank;
+                       !c->tun.rz_member_cap && c->bucket_bits > c->log2_phi &&
+                       dense_lds + kDenseStaticLds <= c->max_lds_rank &&
+                       ((per_cell >= 64.0 && g.n_cot > 64) ||
+                        rz_records_bound(c, h, peak_capacity, capacity) <= uint64_t(32) * uint32_t(c->n_cu));
     // the fast kernel pads member lists with a spare layer (n_layers < 16)
     if (dense || (c->rz_fast && !c->tun.rz_slow_path && fast_lds <= c->max_lds && g.n_layers < kMaxLayers)) {
         P.hw = hw;

@@ -65,3 +65,34 @@ def test_dense_rz_counts_around_255(H, copies):  # noqa: F811
     res, _ = check(H, spec, [(np.concatenate([layer] * copies + [nl]), np.concatenate([phi] * copies + [nphi]),
                               np.concatenate([z] * copies + [nz]))])
     assert H.rz_numpy(res["rz"], res["roff"], 0)["count"].max() >= 10 * copies
+
+
+@pytest.mark.parametrize("sizes,kw", [
+    ([300, 0, 41], dict(n_phi=64, n_qpt=6)),                       # a few members per cell
+    ([900], dict(n_phi=128, n_qpt=5, n_cot=300, n_z0=39)),
+    ([500, 700], dict(n_phi=128, n_qpt=5, n_cot=20, rz_max_candidates=17)),
+])
+def test_short_lists_around_the_choice(H, sizes, kw):  # noqa: F811
+    """Candidate lists bounded by 32 per compute unit take the same form
+    whatever the members; one more takes the other: the same records."""
+    import torch
+    spec = small_spec(threshold=4, **kw)
+    rng = np.random.default_rng(sum(sizes))
+    batch = synth.concat_events([noise_event(rng, n) for n in sizes])
+    hits = H.DeviceHits.from_batch(batch)
+    E = batch.n_events
+    ctx = H.HoughContext(spec, max_events=E, max_hits=batch.n_hits)
+    acc = ctx.vote(hits)
+    pk, poff = ctx.peaks(acc, E)
+    bound = 32 * torch.cuda.get_device_properties(0).multi_processor_count
+    res = [ctx.rz_refine(hits, pk, poff, capacity=cap) for cap in (bound, bound + 1)]
+    torch.cuda.synchronize()
+    if not spec["rz_max_candidates"]:
+        tab = oracle.Tables(spec)
+        for rz, roff in res:
+            for e in range(E):
+                check_event(H, tab, dict(acc=acc, pk=pk, poff=poff, rz=rz, roff=roff), batch, e, rz=True)
+    for e in range(E):
+        a, b = (H.rz_numpy(rz, roff, e) for rz, roff in res)
+        np.testing.assert_array_equal(a, b)
+    assert int(H.offsets_numpy(res[0][1])[-1]) > 10
