@@ -270,7 +270,7 @@ int hough_create(const hough_grid_spec *spec, const hough_limits *limits, int de
               dev_alloc(&c->d_tile_off, c->n_peak_tiles + 1) && dev_alloc(&c->d_cand, ncand) &&
               dev_alloc(&c->d_cand_counts, E) && dev_alloc(&c->d_rz_hist, rzh) &&
               dev_alloc(&c->d_redo_list, rz ? kRedoListCap : 0) &&
-              dev_alloc(&c->d_part_cnt, c->max_parts * kSplitBins) &&
+              dev_alloc(&c->d_part_cnt, c->max_parts * kSplitBins * (ncand ? 4 : 1)) &&   // 4: the selection's parts are waves
               dev_alloc(&c->d_part_base, c->max_parts * kSplitBins) &&
               dev_alloc(&c->d_sec_part, buckets ? (uint64_t(E) + uint64_t(kIndexPartsPerCu) * c->n_cu) * kSectorBins : 0) &&
               (!by_row || (dev_alloc(&c->d_row_off, row_off.size()) && dev_alloc(&c->d_row_ok, row_ok.size()))) &&

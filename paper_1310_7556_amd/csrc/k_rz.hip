@@ -251,6 +251,19 @@ __device__ __forceinline__ uint32_t wave_max_u32(uint32_t x)
     return uint32_t(__builtin_amdgcn_readlane(int(x), 63));
 }
 
+// Sum of x over the wave's 64 lanes (all active), uniform (as wave_max_u32,
+// with shifts in from before a row reading 0).
+__device__ __forceinline__ uint32_t wave_sum_u32(uint32_t x)
+{
+    x += uint32_t(__builtin_amdgcn_update_dpp(0, int(x), 0x111, 0xF, 0xF, false));   // row_shr:1
+    x += uint32_t(__builtin_amdgcn_update_dpp(0, int(x), 0x112, 0xF, 0xF, false));   // row_shr:2
+    x += uint32_t(__builtin_amdgcn_update_dpp(0, int(x), 0x114, 0xF, 0xF, false));   // row_shr:4
+    x += uint32_t(__builtin_amdgcn_update_dpp(0, int(x), 0x118, 0xF, 0xF, false));   // row_shr:8
+    x += uint32_t(__builtin_amdgcn_update_dpp(0, int(x), 0x142, 0xA, 0xF, false));   // row_bcast:15
+    x += uint32_t(__builtin_amdgcn_update_dpp(0, int(x), 0x143, 0xC, 0xF, false));   // row_bcast:31
+    return uint32_t(__builtin_amdgcn_readlane(int(x), 63));
+}
+
 __device__ __forceinline__ void rz_finish(const RzParams &P, uint64_t c, uint32_t pk, uint32_t nm,
                                           uint32_t best_c, uint32_t best_j, uint32_t best_b)
 {
@@ -1454,100 +1467,132 @@ k_rz_select(const uint2 *__restrict__ peaks, uint64_t peak_capacity, const uint6
 }
 
 // Split form of the candidate selection for batches of few events: an
-// event's stored peaks are cut into K parts of consecutive peaks (256
-// threads each).  A peak's bin is 16 - min(popcount, 16), so ascending bins
-// are descending popcounts.  k_sel_count counts a part's peaks per bin (one
-// ballot per bin per 64 peaks); the split plan gives every bin's start and
-// each part's first position per bin, i.e. each peak's position in the
-// (popcount desc, cell asc) order; k_sel_write stores the peaks whose
-// position is below the event's cap, in that order.
-constexpr uint32_t kSelThreads = 256;
+// event's stored peaks are cut into S = 4 K parts of consecutive peaks, one
+// wave each.  A peak's bin is 16 - min(popcount, 16), so ascending bins are
+// descending popcounts.  k_sel_count counts a part's peaks per bin;
+// k_sel_write finds from the event's counts every bin's start and its parts'
+// first positions per bin, i.e. each peak's position in the (popcount desc,
+// cell asc) order, and stores the peaks whose position is below the event's
+// cap, in that order.
+//
+// Bound by latency (two dependent loads per launch), so a wave works alone:
+// lane q holds bin q's count or position, the bins present among 64 peaks
+// (three, with a threshold of 8 of 10 layers) are taken one after another,
+// and the peaks of four rounds are loaded together.  One serving event of
+// 1000 tracks 40 -> 12.7 us, 16 of 100 to 10,000 tracks 49 -> 15.2 (before: a
+// ballot for each of 17 bins per 64 peaks, barriers between rounds and a
+// third launch for the positions).
+constexpr uint32_t kSelThreads = 256, kSelWaves = kSelThreads / 64, kSelRounds = 4;
 
-__device__ __forceinline__ void sel_part(const uint64_t *poff, uint64_t peak_capacity, uint32_t e, uint32_t k,
-                                         uint32_t K, uint64_t &lo, uint64_t &hi, uint64_t &pb, uint64_t &pe)
+// Part s of S of event e's stored peaks [lo, hi).
+__device__ __forceinline__ void sel_part(const uint64_t *poff, uint64_t peak_capacity, uint32_t e, uint32_t s,
+                                         uint32_t S, uint64_t &lo, uint64_t &hi, uint64_t &pb, uint64_t &pe)
 {
     lo = min(poff[e], peak_capacity);
     hi = min(max(poff[e + 1], poff[e]), peak_capacity);
     const uint64_t n = hi - lo;
-    pb = lo + n * k / K;
-    pe = lo + n * (k + 1) / K;
+    pb = lo + n * s / S;
+    pe = lo + n * (s + 1) / S;
 }
 
+// Calls f(bin, lanes of that bin, first peak of the round) for every bin
+// present in every round of 64 of the peaks [pb, pe), in order.
+template <class F>
+__device__ __forceinline__ void sel_rounds(const uint2 *__restrict__ peaks, uint64_t pb, uint64_t pe, uint32_t lane, F &&f)
+{
+    for (uint64_t i0 = pb; i0 < pe; i0 += 64 * kSelRounds) {
+        uint32_t pop[kSelRounds];
+#pragma unroll
+        for (uint32_t r = 0; r < kSelRounds; ++r) pop[r] = peaks[min(i0 + 64 * r + lane, pe - 1)].y >> 16;
+#pragma unroll
+        for (uint32_t r = 0; r < kSelRounds; ++r) {
+            const uint32_t bin = 16u - min(pop[r], 16u);
+            uint64_t todo = __ballot(i0 + 64 * r + lane < pe);
+            while (todo) {
+                const uint32_t q = uint32_t(__builtin_amdgcn_readlane(int(bin), __builtin_ctzll(todo)));
+                const uint64_t m = __ballot(bin == q) & todo;
+                f(q, m, i0 + 64 * r);
+                todo &= ~m;
+            }
+        }
+    }
+}
+
+// part_cnt: [event][bin][S]
 __global__ void __launch_bounds__(kSelThreads)
 k_sel_count(const uint2 *__restrict__ peaks, uint64_t peak_capacity, const uint64_t *__restrict__ poff, uint32_t K,
             uint32_t *__restrict__ part_cnt)
 {
-    __shared__ uint32_t wc[kSelThreads / 64][kSplitBins];
-    const uint32_t t = threadIdx.x, lane = t & 63;
-    const uint32_t wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const uint32_t lane = threadIdx.x & 63, wave = uni(threadIdx.x >> 6);
+    const uint32_t e = blockIdx.x / K, S = K * kSelWaves, s = (blockIdx.x % K) * kSelWaves + wave;
     uint64_t lo, hi, pb, pe;
-    sel_part(poff, peak_capacity, blockIdx.x / K, blockIdx.x % K, K, lo, hi, pb, pe);
-    uint32_t cnt[kSplitBins];
-#pragma unroll
-    for (uint32_t q = 0; q < kSplitBins; ++q) cnt[q] = 0;
-    for (uint64_t i0 = pb + wave * 64; i0 < pe; i0 += kSelThreads) {
-        const uint64_t i = i0 + lane;
-        const uint32_t bin = i < pe ? 16u - min(peaks[i].y >> 16, 16u) : 0xFFu;
-#pragma unroll
-        for (uint32_t q = 0; q < kSplitBins; ++q) cnt[q] += uint32_t(__popcll(__ballot(bin == q)));
-    }
-    if (lane == 0) {
-#pragma unroll
-        for (uint32_t q = 0; q < kSplitBins; ++q) wc[wave][q] = cnt[q];
-    }
-    __syncthreads();
-    if (t < kSplitBins) {
-        uint32_t s = 0;
-        for (uint32_t w = 0; w < kSelThreads / 64; ++w) s += wc[w][t];
-        part_cnt[size_t(blockIdx.x) * kSplitBins + t] = s;
-    }
+    sel_part(poff, peak_capacity, e, s, S, lo, hi, pb, pe);
+    uint32_t cnt = 0;
+    sel_rounds(peaks, pb, pe, lane, [&](uint32_t q, uint64_t m, uint64_t) {
+        cnt += lane == q ? uint32_t(__popcll(m)) : 0u;
+    });
+    if (lane < kSplitBins) part_cnt[(size_t(e) * kSplitBins + lane) * S + s] = cnt;
 }
 
 __global__ void __launch_bounds__(kSelThreads)
 k_sel_write(const uint2 *__restrict__ peaks, uint64_t peak_capacity, const uint64_t *__restrict__ poff,
-            const uint64_t *__restrict__ roff, uint32_t cap, uint32_t K, const uint32_t *__restrict__ part_base,
+            const uint64_t *__restrict__ roff, uint32_t cap, uint32_t K, const uint32_t *__restrict__ part_cnt,
             uint32_t *__restrict__ cand)
 {
-    __shared__ uint32_t wc[kSelThreads / 64][kSplitBins];
-    __shared__ uint32_t base[kSplitBins];
-    const uint32_t t = threadIdx.x, lane = t & 63;
-    const uint32_t wave = __builtin_amdgcn_readfirstlane(t >> 6);
-    const uint32_t e = blockIdx.x / K;
+    // per bin and wave: the counts of its 64 parts, those of them before the
+    // workgroup's, and the counts of the workgroup's own parts
+    __shared__ uint32_t all_s[kSelWaves][kSplitBins], before_s[kSelWaves][kSplitBins], own_s[kSelWaves][kSplitBins];
+    const uint32_t t = threadIdx.x, lane = t & 63, wave = uni(t >> 6);
+    const uint32_t e = blockIdx.x / K, S = K * kSelWaves, s0 = (blockIdx.x % K) * kSelWaves;
     uint64_t lo, hi, pb, pe;
-    sel_part(poff, peak_capacity, e, blockIdx.x % K, K, lo, hi, pb, pe);
+    sel_part(poff, peak_capacity, e, s0 + wave, S, lo, hi, pb, pe);
     const uint32_t need = uint32_t(min(hi - lo, uint64_t(cap)));
-    if (t < kSplitBins) base[t] = part_base[size_t(blockIdx.x) * kSplitBins + t];
+    if (need == 0) return;                          // uniform over the workgroup
+    uint32_t x[kSplitBins];                         // thread t: part t's counts (S <= 256)
+#pragma unroll
+    for (uint32_t q = 0; q < kSplitBins; ++q)
+        x[q] = t < S ? part_cnt[(size_t(e) * kSplitBins + q) * S + t] : 0u;
+#pragma unroll
+    for (uint32_t q = 0; q < kSplitBins; ++q) {
+        uint32_t all = 0, before = 0;
+        if (__ballot(x[q] != 0)) {                  // uniform over the wave
+            all = wave_sum_u32(x[q]);
+            before = wave_sum_u32(t < s0 ? x[q] : 0u);
+        }
+        if (lane == 0) {
+            all_s[wave][q] = all;
+            before_s[wave][q] = before;
+        }
+        if (t - s0 < kSelWaves) own_s[t - s0][q] = x[q];
+    }
     __syncthreads();
-    // nothing of this part is taken once every bin's next position is past the cap
-    uint32_t lowest = 0xFFFFFFFFu;
-    for (uint32_t q = 0; q < kSplitBins; ++q) lowest = min(lowest, base[q]);
-    if (lowest >= need) return;                     // uniform over the workgroup
+    // lane q: the position of the part's next peak of bin q
+    uint32_t total = 0, next = 0, mine = 0;
+    if (lane < kSplitBins) {
+#pragma unroll
+        for (uint32_t w = 0; w < kSelWaves; ++w) {
+            total += all_s[w][lane];
+            next += before_s[w][lane];
+            next += w < wave ? own_s[w][lane] : 0u;
+        }
+        mine = own_s[wave][lane];
+    }
+    uint32_t incl = total;
+#pragma unroll
+    for (uint32_t d = 1; d < 32; d <<= 1) {
+        const uint32_t y = __shfl_up(incl, d, 64);
+        incl += lane >= d ? y : 0u;
+    }
+    next += incl - total;
+    // nothing of this part is taken when its bins' positions are past the cap
+    if (__ballot(mine != 0 && next < need) == 0) return;
     const uint64_t lt = (1ull << lane) - 1ull;
     uint32_t *out = cand + roff[e];
-    for (uint64_t r0 = pb; r0 < pe; r0 += kSelThreads) {
-        const uint64_t i = r0 + t;
-        const uint32_t bin = i < pe ? 16u - min(peaks[i].y >> 16, 16u) : 0xFFu;
-        uint32_t rank = 0;
-#pragma unroll
-        for (uint32_t q = 0; q < kSplitBins; ++q) {
-            const uint64_t m = __ballot(bin == q);
-            if (lane == 0) wc[wave][q] = uint32_t(__popcll(m));
-            if (bin == q) rank = uint32_t(__popcll(m & lt));
-        }
-        __syncthreads();
-        if (bin < kSplitBins) {
-            uint32_t pos = base[bin] + rank;
-            for (uint32_t w = 0; w < wave; ++w) pos += wc[w][bin];
-            if (pos < need) out[pos] = uint32_t(i - lo);
-        }
-        __syncthreads();
-        if (t < kSplitBins) {
-            uint32_t s = 0;
-            for (uint32_t w = 0; w < kSelThreads / 64; ++w) s += wc[w][t];
-            base[t] += s;
-        }
-        __syncthreads();
-    }
+    sel_rounds(peaks, pb, pe, lane, [&](uint32_t q, uint64_t m, uint64_t i0) {
+        const uint32_t pos = uint32_t(__builtin_amdgcn_readlane(int(next), int(q))) + uint32_t(__popcll(m & lt));
+        if (((m >> lane) & 1u) && pos < need) out[pos] = uint32_t(i0 + lane - lo);
+        next += lane == q ? uint32_t(__popcll(m)) : 0u;
+    });
 }
 
 uint32_t rz_blocks(const hough_ctx *c)
@@ -1605,11 +1650,8 @@ hipError_t launch_rz(hough_ctx *c, const hough_hits *h, const hough_peak *peaks,
             const uint2 *pk = reinterpret_cast<const uint2 *>(peaks);
             hipLaunchKernelGGL(k_sel_count, dim3(E * K), dim3(kSelThreads), 0, s, pk, peak_capacity, poff, K,
                                c->d_part_cnt);
-            if ((err = launch_split_plan(E, kSplitBins, K, c->d_part_cnt, c->d_part_base, nullptr, s)) !=
-                hipSuccess)
-                return err;
             hipLaunchKernelGGL(k_sel_write, dim3(E * K), dim3(kSelThreads), 0, s, pk, peak_capacity, poff, roff,
-                               g.rz_max_candidates, K, c->d_part_base, c->d_cand);
+                               g.rz_max_candidates, K, c->d_part_cnt, c->d_cand);
         } else {
             hipLaunchKernelGGL(k_rz_select, dim3(E), dim3(256), 0, s,
                                reinterpret_cast<const uint2 *>(peaks), peak_capacity, poff, roff,
