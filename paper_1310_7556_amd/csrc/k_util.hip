@@ -115,7 +115,13 @@ k_scan_apply(const uint32_t *__restrict__ counts, uint64_t n, const uint64_t *__
 }
 
 // Copies event i's hits from [src_off[i], +len[i]) to [dst_off[i], +len[i]).
-// blockIdx.y strides over events, (blockIdx.x, threadIdx.x) over hits.
+// blockIdx.y strides over events, (blockIdx.x, threadIdx.x) over hits, four
+// per thread and step, loaded together (source and destination share no
+// alignment, so a hit's fields go one by one).  Bound by latency on a skewed
+// batch, whose largest event decides: 16 events of 100 to 10,000 tracks 21 ->
+// 7.5 us.
+constexpr uint32_t kGatherBatch = 4;
+
 __global__ void __launch_bounds__(256)
 k_gather_events(const uint8_t *__restrict__ sl, const uint32_t *__restrict__ sp, const int32_t *__restrict__ sz,
                 const uint64_t *__restrict__ src_off, const uint64_t *__restrict__ len,
@@ -125,11 +131,27 @@ k_gather_events(const uint8_t *__restrict__ sl, const uint32_t *__restrict__ sp,
     for (uint32_t e = blockIdx.y; e < n; e += gridDim.y) {
         const uint64_t s0 = src_off[e], d0 = min(dst_off[e], cap);
         const uint64_t m = min(len[e], cap - d0);   // nothing lands at or past cap
-        for (uint64_t i = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x; i < m;
-             i += uint64_t(gridDim.x) * blockDim.x) {
-            dl[d0 + i] = sl[s0 + i];
-            dp[d0 + i] = sp[s0 + i];
-            if (sz) dz[d0 + i] = sz[s0 + i];
+        const uint64_t step = uint64_t(gridDim.x) * blockDim.x;
+        for (uint64_t i = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x; i < m; i += kGatherBatch * step) {
+            uint8_t l[kGatherBatch];
+            uint32_t p[kGatherBatch];
+            int32_t z[kGatherBatch];
+#pragma unroll
+            for (uint32_t k = 0; k < kGatherBatch; ++k) {
+                const uint64_t j = s0 + min(i + k * step, m - 1);
+                l[k] = sl[j];
+                p[k] = sp[j];
+                z[k] = sz ? sz[j] : 0;
+            }
+#pragma unroll
+            for (uint32_t k = 0; k < kGatherBatch; ++k) {
+                const uint64_t j = i + k * step;
+                if (j < m) {
+                    dl[d0 + j] = l[k];
+                    dp[d0 + j] = p[k];
+                    if (sz) dz[d0 + j] = z[k];
+                }
+            }
         }
     }
 }
@@ -139,7 +161,7 @@ hipError_t launch_gather_events(const uint8_t *sl, const uint32_t *sp, const int
                                 uint32_t *dp, int32_t *dz, uint64_t cap, hipStream_t s)
 {
     if (n == 0 || cap == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_gather_events, dim3(64, std::min(n, 65535u)), dim3(256), 0, s, sl, sp, sz, src_off, len,
+    hipLaunchKernelGGL(k_gather_events, dim3(n < 64 ? 256 : 64, std::min(n, 65535u)), dim3(256), 0, s, sl, sp, sz, src_off, len,
                        dst_off, n, dl, dp, dz, cap);
     return hipGetLastError();
 }
