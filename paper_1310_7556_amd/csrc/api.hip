@@ -51,7 +51,7 @@ void free_all(hough_ctx *c)
                     c->d_tile_off, c->d_cand, c->d_cand_counts, c->d_rz_hist, c->d_redo_list, c->d_gap_info, c->d_gap_list,
                     c->d_scan_part, c->d_scan_off, c->d_dir_tab, c->d_cl_rank, c->d_cl_part,
                     c->d_cl_part_off, c->d_part_cnt, c->d_part_base,
-                    c->d_sec_part, c->d_sec_off, c->d_peak_state, c->d_row_off, c->d_row_ok};
+                    c->d_sec_part, c->d_sec_off, c->d_peak_state, c->d_row_off, c->d_row_ok, c->d_bounds_part};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
     for (auto &t : c->pending) {
@@ -257,6 +257,8 @@ int hough_create(const hough_grid_spec *spec, const hough_limits *limits, int de
     // split_parts keeps E * K <= E + kSplitPartsPerCu * n_cu (K <= ceil(4 n_cu / E))
     c->max_parts = uint64_t(E) + uint64_t(kSplitPartsPerCu) * c->n_cu;
     c->n_peak_state = peaks_one_states(*spec, E);
+    c->n_bounds_parts = H < kBoundsSplitDensity * L * spec->n_phi ? 0
+                        : std::min<uint64_t>(2 * uint64_t(c->n_cu), kBoundsPartBytes / (uint64_t(L) * spec->n_phi * 8));
     const size_t nb = buckets ? (size_t(1) << c->bucket_bits) + 1 : 0;
     const size_t ncand = rz ? size_t(E) * spec->rz_max_candidates : 0;
     const size_t rzh = rz ? size_t(c->n_cu) * kMaxRzWavesPerCu * spec->n_z0 : 0;
@@ -274,6 +276,7 @@ int hough_create(const hough_grid_spec *spec, const hough_limits *limits, int de
               dev_alloc(&c->d_part_base, c->max_parts * kSplitBins) &&
               dev_alloc(&c->d_sec_part, buckets ? (uint64_t(E) + uint64_t(kIndexPartsPerCu) * c->n_cu) * kSectorBins : 0) &&
               (!by_row || (dev_alloc(&c->d_row_off, row_off.size()) && dev_alloc(&c->d_row_ok, row_ok.size()))) &&
+              dev_alloc(&c->d_bounds_part, c->n_bounds_parts * L * spec->n_phi) &&
               dev_alloc(&c->d_peak_state, 2 * c->n_peak_state) &&
               dev_alloc(&c->d_sec_off, buckets ? size_t(E) * (kSectorBins + 1) : 0) &&
               dev_alloc(&c->d_gap_info, size_t(E) * L) && dev_alloc(&c->d_gap_list, H) &&

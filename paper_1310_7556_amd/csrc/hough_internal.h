@@ -45,6 +45,10 @@ struct KernelStat {
 // Most cells the row form of the vote is chosen for (rows_vote_default).
 constexpr uint64_t kRowsCellsMax = uint64_t(1) << 22;
 
+// Mean hits per (layer, bucket) from which an event's bucket bounds are found
+// in parts, and the bytes the partial tables may take.
+constexpr uint64_t kBoundsSplitDensity = 16, kBoundsPartBytes = uint64_t(32) << 20;
+
 struct hough_ctx {
     hough_grid_spec spec{};
     hough_limits lim{};
@@ -98,6 +102,8 @@ struct hough_ctx {
     uint64_t *d_scan_part = nullptr;   // [scan_blocks_max] block sums of a multi-block scan
     uint64_t *d_scan_off = nullptr;    // [scan_blocks_max + 1] their exclusive prefix
     uint64_t scan_blocks_max = 0;
+    uint2 *d_bounds_part = nullptr;    // [n_bounds_parts][L][n_phi] {min, max} of the parts of events of many hits
+    uint64_t n_bounds_parts = 0;
     uint2 *d_dir_tab = nullptr;        // [max_events][L][n_phi] direct vote: per-bucket {lo, span}
     uint32_t *d_rk_info = nullptr;     // [rows][32] rank vote: J | unreachable << 31, then (0x80 + rank) x 0x01010101
     uint32_t *d_rk_sorted = nullptr;   // rank vote: [tiles][L][kRankSortStride] sorted fine offsets, then

@@ -15,8 +15,9 @@
 // occupied iff (f - lo_j) mod 2^32 > span_j, one subtract and one compare.
 // The result is bit-identical to the per-hit vote.
 //
-// k_vote_bounds (one workgroup per event): bucket minima and maxima with LDS
-// atomics, then the table.  k_vote_direct (grid-stride over items of one
+// k_vote_bounds (one workgroup per event; for few events k_vote_bounds_layer
+// or, of many hits each, k_bounds_part and k_bounds_join): bucket minima and
+// maxima with LDS atomics, then the table.  k_vote_direct (grid-stride over items of one
 // event and a run of R-row tiles): the event's table is staged in LDS once
 // per item; in a tile every lane owns one cell column and walks the R rows,
 // building each row's layer mask in a register; the bucket a lane reads for
@@ -89,6 +90,53 @@ __device__ __forceinline__ void shift_in_occupied4(uint32_t (&m)[4], uint32_t f,
 #endif
 }
 
+constexpr uint32_t kBoundsQuads = 4;                 // four-hit loads in flight per thread
+
+// As event_hits, but with `vec` kBoundsQuads loads are issued before the first
+// is used (calls past the end have layer 255).
+template <class F>
+__device__ __forceinline__ void batched_hits(const uint8_t *__restrict__ layer, const uint32_t *__restrict__ phi,
+                                             uint64_t b, uint64_t end, uint32_t t, uint32_t nt, bool vec, F &&take)
+{
+    uint64_t tail = b;
+    if (vec) {
+        const uint64_t a = min((b + 3) & ~uint64_t(3), end);
+        if (t < a - b) take(uint32_t(layer[b + t]), phi[b + t]);
+        const uint64_t nq = (end - a) >> 2;
+        const uint32_t *l4 = reinterpret_cast<const uint32_t *>(layer + a);
+        const uint4 *p4 = reinterpret_cast<const uint4 *>(phi + a);
+        for (uint64_t q = t; q < nq; q += kBoundsQuads * nt) {
+            uint32_t lw[kBoundsQuads];
+            uint4 pw[kBoundsQuads];
+#pragma unroll
+            for (uint32_t i = 0; i < kBoundsQuads; ++i) {
+                const uint64_t k = min(q + i * nt, nq - 1);
+                lw[i] = q + i * nt < nq ? l4[k] : 0xFFFFFFFFu;
+                pw[i] = p4[k];
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (uint32_t i = 0; i < kBoundsQuads; ++i) {
+                take(lw[i] & 0xFFu, pw[i].x);
+                take((lw[i] >> 8) & 0xFFu, pw[i].y);
+                take((lw[i] >> 16) & 0xFFu, pw[i].z);
+                take(lw[i] >> 24, pw[i].w);
+            }
+        }
+        tail = a + (nq << 2);
+    }
+    for (uint64_t i = tail + t; i < end; i += nt) take(uint32_t(layer[i]), phi[i]);
+}
+
+// The table entry of a bucket with hits in [mn, mx] (mn > mx: empty) before a
+// bucket whose smallest is nn (nx < nn: empty).
+__device__ __forceinline__ uint2 bounds_entry(uint32_t mn, uint32_t mx, uint32_t nn, uint32_t nx, uint32_t wmask)
+{
+    const uint32_t lo = mn <= mx ? (mx & wmask) + 1u : 0u;           // may equal W: never empty
+    const uint32_t hi = nn <= nx ? (nn & wmask) : wmask;
+    return hi >= lo ? make_uint2(lo, hi - lo) : make_uint2(0xFFFFFFFFu, 0u);
+}
+
 }  // namespace
 
 // tab[e][l][j] = {lo_j, span_j} as defined above.  Layers are processed in
@@ -96,7 +144,7 @@ __device__ __forceinline__ void shift_in_occupied4(uint32_t (&m)[4], uint32_t f,
 __global__ void __launch_bounds__(1024)
 k_vote_bounds(const uint8_t *__restrict__ layer, const uint32_t *__restrict__ phi,
               const uint64_t *__restrict__ offs, uint64_t n_hits, uint32_t n_layers, uint32_t nphi,
-              uint32_t log2phi, uint32_t shift, uint32_t group_layers, int vec, uint2 *__restrict__ tab)
+              uint32_t shift, uint32_t group_layers, int vec, uint2 *__restrict__ tab)
 {
     HOUGH_DYNAMIC_LDS(uint32_t, lds);                // bmin[gl][nphi], bmax[gl][nphi]
     const uint32_t e = blockIdx.x, t = threadIdx.x, nt = blockDim.x;
@@ -122,26 +170,20 @@ k_vote_bounds(const uint8_t *__restrict__ layer, const uint32_t *__restrict__ ph
         __syncthreads();
         uint2 *out = tab + (size_t(e) * n_layers + l0) * nphi;
         for (uint32_t i = t; i < gl * nphi; i += nt) {
-            const uint32_t ll = i >> log2phi, j = i & (nphi - 1);
-            const uint32_t jn = ll * nphi + ((j + 1) & (nphi - 1));
-            const bool ne = bmin[i] <= bmax[i], ne1 = bmin[jn] <= bmax[jn];
-            const uint32_t lo = ne ? (bmax[i] & wmask) + 1u : 0u;    // may equal W: never empty
-            const uint32_t hi = ne1 ? (bmin[jn] & wmask) : wmask;
-            out[i] = hi >= lo ? make_uint2(lo, hi - lo) : make_uint2(0xFFFFFFFFu, 0u);
+            const uint32_t jn = (i & ~(nphi - 1)) + ((i + 1) & (nphi - 1));
+            out[i] = bounds_entry(bmin[i], bmax[i], bmin[jn], bmax[jn], wmask);
         }
         __syncthreads();
     }
 }
-
-constexpr uint32_t kBoundsQuads = 4;                 // four-hit loads in flight per thread
 
 // k_vote_bounds for few events, a workgroup per (event, layer): every
 // workgroup walks all of the event's hits and keeps those of its own layer,
 // so the rows are written without a merge and L times as many compute units
 // take part.  Bound by the latency of the hit loads, hence the batches of
 // kBoundsQuads (16 events of 150k hits on 10 x 512 entries: 18.5 us, 30 with
-// one load at a time, 64 in the split form below; one event of 20k hits on 10
-// x 1024: 6.8 us, 12 in one workgroup).
+// one load at a time; one event of 20k hits on 10 x 1024: 6.8 us, 12 in one
+// workgroup).
 __global__ void __launch_bounds__(1024)
 k_vote_bounds_layer(const uint8_t *__restrict__ layer, const uint32_t *__restrict__ phi,
                     const uint64_t *__restrict__ offs, uint64_t n_hits, uint32_t n_layers, uint32_t nphi,
@@ -158,75 +200,40 @@ k_vote_bounds_layer(const uint8_t *__restrict__ layer, const uint32_t *__restric
         bmax[j] = 0u;
     }
     __syncthreads();
-    auto take = [&](uint32_t l, uint32_t ph) {
+    batched_hits(layer, phi, b, end, t, nt, vec, [&](uint32_t l, uint32_t ph) {
         if (l == own) {
             atomicMin(&bmin[ph >> shift], ph);
             atomicMax(&bmax[ph >> shift], ph);
         }
-    };
-    uint64_t tail = b;
-    if (vec) {
-        const uint64_t a = min((b + 3) & ~uint64_t(3), end);
-        if (t < a - b) take(layer[b + t], phi[b + t]);
-        const uint64_t nq = (end - a) >> 2;
-        const uint32_t *l4 = reinterpret_cast<const uint32_t *>(layer + a);
-        const uint4 *p4 = reinterpret_cast<const uint4 *>(phi + a);
-        for (uint64_t q = t; q < nq; q += kBoundsQuads * nt) {
-            uint32_t lw[kBoundsQuads];
-            uint4 pw[kBoundsQuads];
-#pragma unroll
-            for (uint32_t i = 0; i < kBoundsQuads; ++i) {
-                const uint64_t k = min(q + i * nt, nq - 1);
-                lw[i] = q + i * nt < nq ? l4[k] : 0xFFFFFFFFu;   // layer 255: nobody's own
-                pw[i] = p4[k];
-            }
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (uint32_t i = 0; i < kBoundsQuads; ++i) {
-                take(lw[i] & 0xFFu, pw[i].x);
-                take((lw[i] >> 8) & 0xFFu, pw[i].y);
-                take((lw[i] >> 16) & 0xFFu, pw[i].z);
-                take(lw[i] >> 24, pw[i].w);
-            }
-        }
-        tail = a + (nq << 2);
-    }
-    for (uint64_t i = tail + t; i < end; i += nt) take(layer[i], phi[i]);
+    });
     __syncthreads();
     uint2 *out = tab + size_t(blockIdx.x) * nphi;
     for (uint32_t j = t; j < nphi; j += nt) {
         const uint32_t jn = (j + 1) & (nphi - 1);
-        const bool ne = bmin[j] <= bmax[j], ne1 = bmin[jn] <= bmax[jn];
-        const uint32_t lo = ne ? (bmax[j] & wmask) + 1u : 0u;        // may equal W: never empty
-        const uint32_t hi = ne1 ? (bmin[jn] & wmask) : wmask;
-        out[j] = hi >= lo ? make_uint2(lo, hi - lo) : make_uint2(0xFFFFFFFFu, 0u);
+        out[j] = bounds_entry(bmin[j], bmax[j], bmin[jn], bmax[jn], wmask);
     }
 }
 
-// Split form of k_vote_bounds for batches of few events: the table is first
-// filled with {min, max} = {0xFFFFFFFF, 0}; each of an event's K parts (a
-// workgroup over a K-th of its hits) finds its own minima and maxima in LDS
-// and merges the non-empty ones into the table with global atomic min/max;
-// then one workgroup per (event, layer) turns the row's {min, max} into
-// {lo, span} exactly as k_vote_bounds does.
-__global__ void k_bounds_init(uint2 *__restrict__ tab, uint64_t n)
-{
-    for (uint64_t i = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x; i < n; i += uint64_t(gridDim.x) * blockDim.x)
-        tab[i] = make_uint2(0xFFFFFFFFu, 0u);
-}
+// Split form of k_vote_bounds for events of many hits: each of an event's K
+// parts (a workgroup over a K-th of its hits) writes its own {min, max} per
+// (layer, bucket), then a workgroup per (event, layer) joins the parts' rows
+// and turns them into {lo, span}.  Bound by the passes over the partial
+// tables, so only for many hits (one event of 600k hits: 26 -> 14.6 us
+// against parts merged in the table with global atomics, 16 of 150k 65 -> 20).
+constexpr uint32_t kBoundsPartThreads = 512;
 
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(kBoundsPartThreads)
 k_bounds_part(const uint8_t *__restrict__ layer, const uint32_t *__restrict__ phi,
               const uint64_t *__restrict__ offs, uint64_t n_hits, uint32_t n_layers, uint32_t nphi, uint32_t shift,
-              uint32_t group_layers, uint32_t K, uint2 *__restrict__ tab)
+              uint32_t group_layers, uint32_t K, int vec, uint2 *__restrict__ parts)
 {
     HOUGH_DYNAMIC_LDS(uint32_t, lds);                // bmin[gl][nphi], bmax[gl][nphi]
     const uint32_t e = blockIdx.x / K, k = blockIdx.x % K, t = threadIdx.x, nt = blockDim.x;
-    const uint64_t b0 = min(offs[e], n_hits);
-    uint64_t end0 = min(offs[e + 1], n_hits);
-    if (end0 < b0) end0 = b0;
-    const uint64_t len = end0 - b0;
-    const uint64_t b = b0 + len * k / K, end = b0 + len * (k + 1) / K;
+    uint64_t b, end;
+    event_range(offs, e, n_hits, b, end);
+    const uint64_t len = end - b;
+    end = b + len * (k + 1) / K;
+    b += len * k / K;
     for (uint32_t l0 = 0; l0 < n_layers; l0 += group_layers) {
         const uint32_t gl = min(group_layers, n_layers - l0);
         uint32_t *bmin = lds, *bmax = lds + gl * nphi;
@@ -235,42 +242,43 @@ k_bounds_part(const uint8_t *__restrict__ layer, const uint32_t *__restrict__ ph
             bmax[i] = 0u;
         }
         __syncthreads();
-        for (uint64_t i = b + t; i < end; i += nt) {
-            const uint32_t l = layer[i];
+        batched_hits(layer, phi, b, end, t, nt, vec, [&](uint32_t l, uint32_t ph) {
             if (l >= l0 && l < l0 + gl) {
-                const uint32_t ph = phi[i];
                 const uint32_t bi = (l - l0) * nphi + (ph >> shift);
                 atomicMin(&bmin[bi], ph);
                 atomicMax(&bmax[bi], ph);
             }
-        }
+        });
         __syncthreads();
-        uint2 *out = tab + (size_t(e) * n_layers + l0) * nphi;
-        for (uint32_t i = t; i < gl * nphi; i += nt) {
-            if (bmin[i] <= bmax[i]) {
-                atomicMin(&out[i].x, bmin[i]);
-                atomicMax(&out[i].y, bmax[i]);
-            }
-        }
+        uint2 *out = parts + (size_t(blockIdx.x) * n_layers + l0) * nphi;
+        for (uint32_t i = t; i < gl * nphi; i += nt) out[i] = make_uint2(bmin[i], bmax[i]);
         __syncthreads();
     }
 }
 
-__global__ void __launch_bounds__(256)
-k_bounds_final(uint32_t nphi, uint32_t shift, uint2 *__restrict__ tab)
+__global__ void __launch_bounds__(1024)
+k_bounds_join(const uint2 *__restrict__ parts, uint32_t n_layers, uint32_t nphi, uint32_t shift, uint32_t K,
+              uint2 *__restrict__ tab)
 {
     HOUGH_DYNAMIC_LDS(uint2, row);                   // [nphi] {min, max}
-    const uint32_t t = threadIdx.x, nt = blockDim.x;
+    const uint32_t e = blockIdx.x / n_layers, l = blockIdx.x % n_layers, t = threadIdx.x, nt = blockDim.x;
     const uint32_t wmask = (1u << shift) - 1u;
-    uint2 *r = tab + size_t(blockIdx.x) * nphi;      // one (event, layer) row
-    for (uint32_t j = t; j < nphi; j += nt) row[j] = r[j];
+    const uint2 *in = parts + (size_t(e) * K * n_layers + l) * nphi;
+    const size_t step = size_t(n_layers) * nphi;
+    for (uint32_t j = t; j < nphi; j += nt) {
+        uint2 a = make_uint2(0xFFFFFFFFu, 0u);
+#pragma unroll 8
+        for (uint32_t k = 0; k < K; ++k) {
+            const uint2 x = in[k * step + j];
+            a = make_uint2(min(a.x, x.x), max(a.y, x.y));
+        }
+        row[j] = a;
+    }
     __syncthreads();
+    uint2 *out = tab + size_t(blockIdx.x) * nphi;
     for (uint32_t j = t; j < nphi; j += nt) {
         const uint2 a = row[j], n = row[(j + 1) & (nphi - 1)];
-        const bool ne = a.x <= a.y, ne1 = n.x <= n.y;
-        const uint32_t lo = ne ? (a.y & wmask) + 1u : 0u;        // may equal W: never empty
-        const uint32_t hi = ne1 ? (n.x & wmask) : wmask;
-        r[j] = hi >= lo ? make_uint2(lo, hi - lo) : make_uint2(0xFFFFFFFFu, 0u);
+        out[j] = bounds_entry(a.x, a.y, n.x, n.y, wmask);
     }
 }
 
@@ -438,35 +446,30 @@ hipError_t launch_vote_bounds(hough_ctx *c, const hough_hits *h, hipStream_t s)
     const int vec = (reinterpret_cast<uintptr_t>(h->layer) & 3) == 0 && (reinterpret_cast<uintptr_t>(h->phi) & 15) == 0;
     KernelTimer t;
     prof_begin(c, "vote_bounds", s, &t);
-    const uint64_t entries = uint64_t(c->spec.n_layers) * c->spec.n_phi;
     const uint64_t per_event = E ? h->n_hits / E : 0;
-    // by layer, but for a few very large events, whose hits are split (the
-    // split form costs two more launches, and each part initialises and merges
-    // its event's whole table): one event of 210k hits 20.1 us by layer and
-    // 20.2 split, of 300k 27 and 21; four of 300k 28.4 and 28.9; 16 of 300k 32
-    // and 71
-    if (bounds_by_layer(c, E) && (per_event <= (1u << 18) || E >= 8)) {
+    // in parts: events of many hits per table entry (16 or more), and so few
+    // of them that each has four parts or more (parts / by layer / per event
+    // in us, 10 x 512 entries: one event of 108k hits 14 / 14 / 18, of 600k
+    // 14.6 / 49 / 71, 16 of 96k 20 / 15 / 18, of 150k 20 / 19 / 23, 50 of 120k
+    // 21 / 40 / 29; 10 x 256: 120 of 120k 24 / 84 / 29, 250 of 90k, two parts
+    // each, 33 / 128 / 26).  Where the means are near the line the largest
+    // event decides: 16 of 100 to 10,000 tracks 15 in parts, 39
+    // by layer.
+    const uint64_t K = std::min<uint64_t>(c->n_bounds_parts / std::max(E, 1u), std::min<uint64_t>(64, per_event / 4096));
+    if (K >= 4 && per_event >= kBoundsSplitDensity * c->spec.n_layers * c->spec.n_phi) {
+        hipLaunchKernelGGL(k_bounds_part, dim3(uint32_t(E * K)), dim3(kBoundsPartThreads),
+                           size_t(group) * c->spec.n_phi * 8, s, h->layer, h->phi, h->event_offsets, h->n_hits,
+                           c->spec.n_layers, c->spec.n_phi, c->shift, group, uint32_t(K), vec, c->d_bounds_part);
+        hipLaunchKernelGGL(k_bounds_join, dim3(E * c->spec.n_layers), dim3(1024), size_t(c->spec.n_phi) * 8, s,
+                           c->d_bounds_part, c->spec.n_layers, c->spec.n_phi, c->shift, uint32_t(K), c->d_dir_tab);
+    } else if (bounds_by_layer(c, E)) {
         hipLaunchKernelGGL(k_vote_bounds_layer, dim3(E * c->spec.n_layers), dim3(1024), size_t(c->spec.n_phi) * 8, s,
                            h->layer, h->phi, h->event_offsets, h->n_hits, c->spec.n_layers, c->spec.n_phi, c->shift,
                            vec, c->d_dir_tab);
-        prof_end(c, s, &t);
-        return hipGetLastError();
-    }
-    // otherwise split events with many hits per table entry (at least 16)
-    const uint32_t K = per_event >= 16 * entries ? split_parts(c, E) : 0;
-    if (K >= 2) {
-        const uint64_t n = uint64_t(E) * entries;
-        hipLaunchKernelGGL(k_bounds_init, dim3(uint32_t(std::min<uint64_t>((n + 255) / 256, 4096))), dim3(256), 0, s,
-                           c->d_dir_tab, n);
-        hipLaunchKernelGGL(k_bounds_part, dim3(E * K), dim3(256), size_t(group) * c->spec.n_phi * 8, s, h->layer,
-                           h->phi, h->event_offsets, h->n_hits, c->spec.n_layers, c->spec.n_phi, c->shift, group, K,
-                           c->d_dir_tab);
-        hipLaunchKernelGGL(k_bounds_final, dim3(E * c->spec.n_layers), dim3(256), size_t(c->spec.n_phi) * 8, s,
-                           c->spec.n_phi, c->shift, c->d_dir_tab);
     } else {
         hipLaunchKernelGGL(k_vote_bounds, dim3(E), dim3(1024), size_t(group) * c->spec.n_phi * 8, s, h->layer,
-                           h->phi, h->event_offsets, h->n_hits, c->spec.n_layers, c->spec.n_phi, c->log2_phi,
-                           c->shift, group, vec, c->d_dir_tab);
+                           h->phi, h->event_offsets, h->n_hits, c->spec.n_layers, c->spec.n_phi, c->shift, group,
+                           vec, c->d_dir_tab);
     }
     prof_end(c, s, &t);
     return hipGetLastError();

@@ -36,7 +36,10 @@ def layers(n):
     ([700] * 52, dict(n_phi=128, n_qpt=33), 0),                 # one more event: the forms before it
     ([4000], dict(n_phi=1024, n_qpt=4096), 0),                  # 2^22 cells, the most it is chosen for
     ([4000], dict(n_phi=1024, n_qpt=4097), 0),
-    ([270000], dict(n_phi=256, n_qpt=37), 0),                   # a very large event: split bounds
+    ([270000], dict(n_phi=256, n_qpt=37), 0),                   # a very large event: bounds in 64 parts
+    ([20000, 0, 3], dict(n_phi=64, n_qpt=5), 1),                # no vector loads, one part each: by layer
+    ([50000, 0, 3], dict(n_phi=64, n_qpt=5), 1),                # four parts, most of them empty
+    ([90000, 7], dict(n_phi=256, n_qpt=9), 0),
     ([1500, 300], dict(n_phi=128, n_qpt=19, **layers(1)), 0),
     ([1500, 300], dict(n_phi=128, n_qpt=19, **layers(7)), 3),
     ([1500, 300], dict(n_phi=128, n_qpt=19, **layers(16)), 0),
