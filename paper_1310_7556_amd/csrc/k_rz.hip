@@ -9,7 +9,8 @@
 //   b = floor((z - Z[k][l][j] - z0_lo) * n_z0 / (z0_hi - z0_lo)),
 // and the record is the argmax over (j, b), ties to the smallest j then b.
 //
-// One 64-wide wavefront per candidate, persistent over a work counter.  A
+// One 64-wide wavefront per candidate, persistent over its share of them or a
+// work counter.  A
 // lane owns cot bins j = lane, lane + 64, ... and a private column of z0
 // counters in LDS; its running maximum is exact because counts only grow.
 //
@@ -57,7 +58,6 @@ struct RzParams {
     uint2 *out4;                  // hough_rz records as 4 x uint32 (2 x uint2)
     uint64_t out_capacity;
     uint32_t *counter;            // the work counter (general kernel); queue q's at counter[q * kRzQueueStride] (fast)
-    uint32_t n_queues;            // fast kernel: work queues, 1 .. kRzQueues
     uint32_t *redo_count;         // records marked for the exact path
     uint64_t *redo_list;          // their indices, the first redo_cap of them
     uint32_t redo_cap;
@@ -76,18 +76,24 @@ struct RzParams {
     uint32_t mcap;                // fast path: member list capacity
 };
 
-// The fast kernel's work queues: the candidates are split into kRzQueues
-// contiguous ranges, one per XCD, each with its own counter (kRzQueueStride
-// dwords apart, in different cache lines); a wave starts on the queue of
-// the XCD it runs on (read from the hardware, as the XCD a workgroup lands
-// on depends on what else runs), so that an XCD's waves share a range:
-// neighbouring cells, whose members and tables are the same cache lines in
-// that XCD's L2.  A wave takes kRzChunk consecutive candidates per ticket
-// and, when its queue is empty, moves on to the next queue (each empty
-// queue costs the wave one ticket, so short record lists -- a micro-batch --
-// use one queue).  (1000-track event: 0.96 ms with 8 queues of 8-candidate tickets;
-// 1.00 ms with one queue, 0.99 and 0.98 ms with tickets of 4 and 16, 1.04
-// and 1.17 ms with 32 and 64 queues.)
+// How the fast kernel hands out candidates.  A list of up to kRzShareMax per
+// wave is divided evenly, a contiguous share for each wave, an XCD's shares
+// side by side: tickets of kRzChunk leave waves idle or with twice the work
+// of others (12 members per cell, 4096 waves: 1024 candidates 95 us by
+// tickets, 23 by shares, 16,384 130 and 54, 43,203 137 and 95, 59,512 190 and
+// 127; 92,778 of 18 249 and 210, 161,779 of 29 459 and 450; 398,477 of 20 865
+// and 909, where the longest share decides).
+// Longer lists are split into kRzQueues contiguous ranges, one per XCD, each
+// with its own counter (kRzQueueStride dwords apart, in different cache
+// lines); a wave starts on the queue of the XCD it runs on (read from the
+// hardware, as the XCD a workgroup lands on depends on what else runs), so
+// that an XCD's waves share a range: neighbouring cells, whose members and
+// tables are the same cache lines in that XCD's L2.  A wave takes kRzChunk
+// consecutive candidates per ticket and, when its queue is empty, moves on
+// to the next queue.  (1000-track event: 0.96 ms with 8 queues of 8-candidate
+// tickets; 1.00 ms with one queue, 0.99 and 0.98 ms with tickets of 4 and 16,
+// 1.04 and 1.17 ms with 32 and 64 queues.)
+constexpr uint32_t kRzShareMax = 64;
 constexpr uint32_t kRzQueues = 8;
 constexpr uint32_t kRzQueueStride = 32;
 constexpr uint32_t kRzChunk = 8;
@@ -453,15 +459,25 @@ k_rz_vote_fast(RzParams P)
     const uint64_t total = min(P.roff[P.n_events], P.out_capacity);
     for (uint32_t i = lane; i < P.hw * 64; i += 64) hist[i] = 0;
     __syncthreads();
-    const uint32_t nq = P.n_queues, q0 = xcd_id();
-    for (uint32_t qi = 0; qi < nq; ++qi) {
-      const uint32_t q = (q0 + qi) % nq;
-      const uint64_t qb = total * q / nq, qe = total * (q + 1) / nq;
+    const uint32_t q0 = xcd_id();
+    const bool shares = total <= uint64_t(kRzShareMax) * gridDim.x;
+    for (uint32_t qi = 0; qi < (shares ? 1u : kRzQueues); ++qi) {
+      const uint32_t q = (q0 + qi) % kRzQueues;
+      const uint64_t qb = total * q / kRzQueues, qe = total * (q + 1) / kRzQueues;
       uint32_t *qc = P.counter + q * kRzQueueStride;
-      for (;;) {
-        const uint64_t c0 = qb + uni(atomicAdd(qc, lane == 0 ? kRzChunk : 0u));
-        if (c0 >= qe) break;
-        const uint64_t c1 = min(c0 + kRzChunk, qe);
+      for (uint32_t round = 0;; ++round) {
+        uint64_t c0, c1;
+        if (shares) {
+            if (round) break;
+            const uint32_t g = gridDim.x, b = blockIdx.x, w = g % kRzQueues ? b : b % kRzQueues * (g / kRzQueues) + b / kRzQueues;
+            c0 = total * w / g;
+            c1 = total * (w + 1) / g;
+            if (c0 == c1) break;
+        } else {
+            c0 = qb + uni(atomicAdd(qc, lane == 0 ? kRzChunk : 0u));
+            if (c0 >= qe) break;
+            c1 = min(c0 + kRzChunk, qe);
+        }
         // the next candidate's peak record is fetched while the current one
         // is processed, so its latency overlaps the current loads
         uint2 nrec = rz_record(P, c0);
@@ -844,8 +860,7 @@ k_rz_vote_fast(RzParams P)
     }
 }
 
-// Dense form of the fast kernel, for cells of many members and for short
-// candidate lists.
+// Dense form of the fast kernel, for cells of many members.
 // One workgroup per candidate: the member list is gathered once, in any
 // order; pass w counts cot bins 64 w .. 64 w + 63 (then + 256), one per lane,
 // and two waves share a pass's counters: each takes every second member and
@@ -1723,35 +1738,29 @@ hipError_t launch_rz(hough_ctx *c, const hough_hits *h, const hough_peak *peaks,
         while (mcap > 256 && size_t(rz_fast_lds_dwords(hw, mcap)) * 4 > c->max_lds) mcap >>= 1;
     }
     const size_t fast_lds = size_t(rz_fast_lds_dwords(hw, mcap)) * 4;
-    // Cells of many members and short candidate lists go to the dense form:
-    // from 64 members per cell on, where its byte counters and list cost less
-    // than the one-wave form's 8-bit counters (251,000 candidates of 53
-    // members 2730 us against 2359, 131,000 of 76 1512 against 1604, 16,384
-    // of 117 230 against 337; with a single pass of 64 cot bins 194 against
-    // 186), and up to 32 candidates per compute unit,
-    // which the one-wave form spreads over too few waves, eight per ticket
-    // (12 to 47 members, 256 x 256 bins: 1024 candidates 19 to 22 us against
-    // 95 to 120, 4096 57 to 62 against 108 to 131, 8192 101 to 107 against
-    // 121 to 144, 16,384 184 to 195 against 130 to 159).  It scans whole
-    // azimuth buckets, so it wants them narrower than a cell (n_phi <=
-    // 2048), and two workgroups per compute unit.  Any rz knob set by hand
-    // keeps the one-wave form.
+    // Cells of many members go to the dense form, more than one pass of cot
+    // bins given: from 64 members per cell on, where its byte counters and
+    // list cost less than the one-wave form's 8-bit counters (251,000
+    // candidates of 53 members 2730 us against 2369, 131,000 of 76 1515
+    // against 1602, 16,384 of 59 208 against 206, of 117 231 against 318),
+    // and up to 16 candidates per compute unit from 48 on (1024 of 47 27
+    // against 38, 4096 61 against 58); with 4-bit counters, below, the
+    // one-wave form is the faster at any length (1024 of 12 23 against 24.5,
+    // 8192 34 against 101).  The dense form scans whole azimuth buckets, so
+    // it wants them narrower than a cell (n_phi <= 2048), and two workgroups
+    // per compute unit.  Any rz knob set by hand keeps the one-wave form.
     const size_t dense_lds = rz_dense_lds(g.n_z0);
     const bool dense = c->rz_fast && !c->tun.rz_slow_path && !c->tun.rz_counter_bits && !c->tun.rz_waves_per_cu &&
                        !c->tun.rz_member_cap && c->bucket_bits > c->log2_phi &&
                        dense_lds + kDenseStaticLds <= c->max_lds_rank &&
-                       ((per_cell >= 64.0 && g.n_cot > 64) ||
-                        rz_records_bound(c, h, peak_capacity, capacity) <= uint64_t(32) * uint32_t(c->n_cu));
+                       g.n_cot > 64 &&
+                       (per_cell >= 64.0 ||
+                        (per_cell >= 48.0 &&
+                         rz_records_bound(c, h, peak_capacity, capacity) <= uint64_t(16) * uint32_t(c->n_cu)));
     // the fast kernel pads member lists with a spare layer (n_layers < 16)
     if (dense || (c->rz_fast && !c->tun.rz_slow_path && fast_lds <= c->max_lds && g.n_layers < kMaxLayers)) {
         P.hw = hw;
         P.mcap = mcap;
-        // one queue per XCD where the records can give every wave several
-        // tickets; one queue for short lists (a micro-batch), whose waves
-        // would spend more on empty tickets than the queues save (16-event
-        // c5 micro-batches served at 17k events/s with 8 queues, 19.7k with
-        // one)
-        P.n_queues = rz_records_bound(c, h, peak_capacity, capacity) >= uint64_t(4) * blocks * kRzChunk ? kRzQueues : 1u;
         P.lds_ok = 0;
         prof_begin(c, "rz_vote", s, &t);
         const int mul = P.bs != 0 ? 1 : (P.span < (1u << 24) && P.bm < (1u << 24)) ? 2 : 0;

@@ -68,31 +68,60 @@ def test_dense_rz_counts_around_255(H, copies):  # noqa: F811
 
 
 @pytest.mark.parametrize("sizes,kw", [
-    ([300, 0, 41], dict(n_phi=64, n_qpt=6)),                       # a few members per cell
-    ([900], dict(n_phi=128, n_qpt=5, n_cot=300, n_z0=39)),
-    ([500, 700], dict(n_phi=128, n_qpt=5, n_cot=20, rz_max_candidates=17)),
+    ([900, 1000, 850], dict(n_phi=16, n_qpt=6)),                   # 48 to 64 members per cell
+    ([900], dict(n_phi=16, n_qpt=5, n_cot=65, n_z0=39)),
+    ([900], dict(n_phi=16, n_qpt=5, n_cot=64)),
 ])
 def test_short_lists_around_the_choice(H, sizes, kw):  # noqa: F811
-    """Candidate lists bounded by 32 per compute unit take the same form
-    whatever the members; one more takes the other: the same records."""
+    """From 48 to 64 members per cell, candidate lists bounded by 16 per
+    compute unit take the dense form, longer ones and those of one pass the
+    other: the same records."""
     import torch
     spec = small_spec(threshold=4, **kw)
     rng = np.random.default_rng(sum(sizes))
     batch = synth.concat_events([noise_event(rng, n) for n in sizes])
+    assert 48 <= batch.n_hits / batch.n_events / spec["n_phi"] < 64
     hits = H.DeviceHits.from_batch(batch)
     E = batch.n_events
     ctx = H.HoughContext(spec, max_events=E, max_hits=batch.n_hits)
     acc = ctx.vote(hits)
     pk, poff = ctx.peaks(acc, E)
-    bound = 32 * torch.cuda.get_device_properties(0).multi_processor_count
+    bound = 16 * torch.cuda.get_device_properties(0).multi_processor_count
     res = [ctx.rz_refine(hits, pk, poff, capacity=cap) for cap in (bound, bound + 1)]
     torch.cuda.synchronize()
-    if not spec["rz_max_candidates"]:
-        tab = oracle.Tables(spec)
-        for rz, roff in res:
-            for e in range(E):
-                check_event(H, tab, dict(acc=acc, pk=pk, poff=poff, rz=rz, roff=roff), batch, e, rz=True)
-    for e in range(E):
-        a, b = (H.rz_numpy(rz, roff, e) for rz, roff in res)
+    tab = oracle.Tables(spec)
+    for rz, roff in res:
+        for e in range(E):
+            check_event(H, tab, dict(acc=acc, pk=pk, poff=poff, rz=rz, roff=roff), batch, e, rz=True)
+
+
+@pytest.mark.parametrize("kw", [dict(n_qpt=300), dict(n_qpt=300, rz_max_candidates=9000), dict(n_qpt=3)])
+def test_shares_and_tickets(H, kw):  # noqa: F811
+    """Lists divided evenly over the waves and lists past 64 per wave (one wave
+    per compute unit), which go by tickets, give the same records; so do a few
+    candidates over many waves."""
+    import torch
+    spec = small_spec(threshold=4, n_phi=256, n_cot=20, n_z0=32, **kw)
+    rng = np.random.default_rng(4)
+    batch = synth.concat_events([noise_event(rng, n) for n in (3000, 0, 2800)])
+    hits = H.DeviceHits.from_batch(batch)
+    ctx = H.HoughContext(spec, max_events=3, max_hits=batch.n_hits)
+    pk, poff = ctx.peaks(ctx.vote(hits), 3)
+    res = []
+    for w in (1, 2, 16):
+        ctx.set_tuning(rz_waves_per_cu=w, rz_counter_bits=4)
+        res.append(ctx.rz_refine(hits, pk, poff))
+    torch.cuda.synchronize()
+    n = [int(H.offsets_numpy(roff)[-1]) for _, roff in res]
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    assert n[0] == n[1] == n[2] and (n[0] > 64 * cus if spec["n_qpt"] == 300 else n[0] < 16 * cus)
+    for e in range(3):
+        a, b, c = (H.rz_numpy(rz, roff, e) for rz, roff in res)
         np.testing.assert_array_equal(a, b)
-    assert int(H.offsets_numpy(res[0][1])[-1]) > 10
+        np.testing.assert_array_equal(a, c)
+    if spec["n_qpt"] == 3:
+        tab = oracle.Tables(spec)
+        ev = batch.event(0)
+        opk = oracle.peaks(tab, oracle.vote_mask(tab, ev.layer, ev.phi))
+        np.testing.assert_array_equal(a_first := H.rz_numpy(*res[0], 0), oracle.rz(tab, ev.layer, ev.phi, ev.z, opk).astype(H.RZ_DTYPE))
+        assert len(a_first)
