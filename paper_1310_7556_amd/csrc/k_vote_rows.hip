@@ -18,13 +18,17 @@
 // where a launch that does nothing takes 4.5 (rank form, tile by tile: 32 and
 // 18; direct form: 12 and 10).  Four layers' entries at a time: all ten of a
 // ten-layer grid take the same 7 to 10 us with 150 registers for 82.
+#include "device_hits.h"
 #include "hough_internal.h"
 
 namespace hough {
 
 namespace {
 
-constexpr uint32_t kRowsThreads = 256;
+constexpr uint32_t kRowsThreads = 256, kRowsWaves = kRowsThreads / 64;
+// What a workgroup that finds the table itself takes: (layer, bucket) entries
+// (20 KB of LDS) and mean hits per event.
+constexpr uint32_t kRowsOwnEntries = 2560, kRowsOwnHits = 8192;
 
 // m[k] = 2 m[k] + [(f - e[k].lo) mod 2^32 > e[k].span] for four cells, f
 // wave-uniform: a subtract, a subtract whose borrow is the comparison, an add
@@ -59,21 +63,20 @@ __device__ __forceinline__ void shift_in4(uint32_t (&m)[4], uint32_t f, const ui
 
 }  // namespace
 
+namespace {
+
+// Rows R tile .. R tile + R - 1 of event e, cells 256 group .. + 255, from the
+// event's table etab.
 template <int R>
-__global__ void __launch_bounds__(kRowsThreads)
-k_vote_rows(const uint2 *__restrict__ tab, const uint32_t *__restrict__ row_off, const uint32_t *__restrict__ row_ok,
-            uint32_t n_layers, uint32_t rows, uint32_t nphi, uint32_t shift, uint32_t n_tiles, uint32_t n_groups,
-            uint64_t n_units, uint16_t *__restrict__ acc)
+__device__ __forceinline__ void rows_unit(const uint2 *etab, const uint32_t *__restrict__ row_off,
+                                          const uint32_t *__restrict__ row_ok, uint32_t n_layers, uint32_t rows,
+                                          uint32_t nphi, uint32_t shift, uint32_t e, uint32_t tile, uint32_t group,
+                                          uint16_t *__restrict__ acc)
 {
     constexpr int B = 4;                             // layers loaded together
     const uint32_t lane = threadIdx.x & 63;
-    const uint64_t unit = uint64_t(blockIdx.x) * (kRowsThreads / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    if (unit >= n_units) return;
-    const uint32_t group = uint32_t(unit % n_groups), tile = uint32_t(unit / n_groups % n_tiles);
-    const uint32_t e = uint32_t(unit / n_groups / n_tiles);
     const uint32_t r0 = tile * R, last = min(r0 + R, rows) - 1;
     const uint32_t p0 = group * 256 + lane * 4, pm = nphi - 1, wmask = (1u << shift) - 1u;
-    const uint2 *etab = tab + size_t(e) * n_layers * nphi;
     // the rows' offsets, 16 layers each (rows past the last repeat it)
     const uint32_t *off[R];
     uint32_t ok[R];
@@ -140,16 +143,86 @@ k_vote_rows(const uint2 *__restrict__ tab, const uint32_t *__restrict__ row_off,
     }
 }
 
+}  // namespace
+
+template <int R>
+__global__ void __launch_bounds__(kRowsThreads)
+k_vote_rows(const uint2 *__restrict__ tab, const uint32_t *__restrict__ row_off, const uint32_t *__restrict__ row_ok,
+            uint32_t n_layers, uint32_t rows, uint32_t nphi, uint32_t shift, uint32_t n_tiles, uint32_t n_groups,
+            uint64_t n_units, uint16_t *__restrict__ acc)
+{
+    const uint64_t unit = uint64_t(blockIdx.x) * kRowsWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (unit >= n_units) return;
+    const uint32_t group = uint32_t(unit % n_groups), tile = uint32_t(unit / n_groups % n_tiles);
+    const uint32_t e = uint32_t(unit / n_groups / n_tiles);
+    rows_unit<R>(tab + size_t(e) * n_layers * nphi, row_off, row_ok, n_layers, rows, nphi, shift, e, tile, group, acc);
+}
+
+// The same for events of few hits on small grids, in one launch: every
+// workgroup finds the event's whole table itself, in LDS, from all of its
+// hits.  Bound by its chain of LDS passes, which takes less than a second
+// launch: bounds and vote of one event of 256 x 256 cells and 2000 hits 10.6 ->
+// 8.9 us, of 64 x 128 11.2 -> 8.3.
+template <int R>
+__global__ void __launch_bounds__(kRowsThreads)
+k_vote_rows_own(const uint8_t *__restrict__ layer, const uint32_t *__restrict__ phi, const uint64_t *__restrict__ offs,
+                uint64_t n_hits, int vec, const uint32_t *__restrict__ row_off, const uint32_t *__restrict__ row_ok,
+                uint32_t n_layers, uint32_t rows, uint32_t nphi, uint32_t shift, uint32_t n_tiles, uint32_t n_groups,
+                uint32_t wgs, uint16_t *__restrict__ acc)
+{
+    HOUGH_DYNAMIC_LDS(uint2, tab_s);                 // [L][nphi]: {min, max}, then {lo, span}
+    const uint32_t t = threadIdx.x, e = blockIdx.x / wgs, entries = n_layers * nphi;
+    const uint32_t unit = (blockIdx.x % wgs) * kRowsWaves + __builtin_amdgcn_readfirstlane(t >> 6);
+    uint64_t b, end;
+    event_range(offs, e, n_hits, b, end);
+    for (uint32_t i = t; i < entries; i += kRowsThreads) tab_s[i] = make_uint2(0xFFFFFFFFu, 0u);
+    __syncthreads();
+    batched_hits(layer, phi, b, end, t, kRowsThreads, vec, [&](uint32_t l, uint32_t ph) {
+        if (l < n_layers) {
+            uint2 *x = &tab_s[l * nphi + (ph >> shift)];
+            atomicMin(&x->x, ph);
+            atomicMax(&x->y, ph);
+        }
+    });
+    __syncthreads();
+    uint2 out[kRowsOwnEntries / kRowsThreads];
+#pragma unroll
+    for (uint32_t k = 0; k < kRowsOwnEntries / kRowsThreads; ++k) {
+        if (k * kRowsThreads >= entries) break;      // uniform
+        const uint32_t i = min(t + k * kRowsThreads, entries - 1);
+        const uint2 a = tab_s[i], n = tab_s[(i & ~(nphi - 1)) + ((i + 1) & (nphi - 1))];
+        out[k] = bounds_entry(a.x, a.y, n.x, n.y, (1u << shift) - 1u);
+    }
+    __syncthreads();
+#pragma unroll
+    for (uint32_t k = 0; k < kRowsOwnEntries / kRowsThreads; ++k) {
+        if (k * kRowsThreads >= entries) break;
+        if (t + k * kRowsThreads < entries) tab_s[t + k * kRowsThreads] = out[k];
+    }
+    __syncthreads();
+    if (unit < n_tiles * n_groups)
+        rows_unit<R>(tab_s, row_off, row_ok, n_layers, rows, nphi, shift, e, unit / n_groups, unit % n_groups, acc);
+}
+
 namespace {
 
 template <int R>
-void launch_rows_r(hough_ctx *c, uint32_t E, uint16_t *acc, hipStream_t s)
+void launch_rows_r(hough_ctx *c, const hough_hits *h, bool own, uint16_t *acc, hipStream_t s)
 {
-    const uint32_t n_tiles = (c->rows + R - 1) / R, n_groups = (c->spec.n_phi + 255) / 256;
-    const uint64_t n_units = uint64_t(E) * n_tiles * n_groups;
-    const dim3 grid(uint32_t((n_units + kRowsThreads / 64 - 1) / (kRowsThreads / 64)));
-    hipLaunchKernelGGL(k_vote_rows<R>, grid, dim3(kRowsThreads), 0, s, c->d_dir_tab, c->d_row_off, c->d_row_ok,
-                       c->spec.n_layers, c->rows, c->spec.n_phi, c->shift, n_tiles, n_groups, n_units, acc);
+    const uint32_t E = h->n_events, n_tiles = (c->rows + R - 1) / R, n_groups = (c->spec.n_phi + 255) / 256;
+    if (own) {
+        const int vec = (reinterpret_cast<uintptr_t>(h->layer) & 3) == 0 && (reinterpret_cast<uintptr_t>(h->phi) & 15) == 0;
+        const uint32_t wgs = (n_tiles * n_groups + kRowsWaves - 1) / kRowsWaves;
+        hipLaunchKernelGGL(k_vote_rows_own<R>, dim3(E * wgs), dim3(kRowsThreads),
+                           size_t(c->spec.n_layers) * c->spec.n_phi * 8, s, h->layer, h->phi, h->event_offsets,
+                           h->n_hits, vec, c->d_row_off, c->d_row_ok, c->spec.n_layers, c->rows, c->spec.n_phi,
+                           c->shift, n_tiles, n_groups, wgs, acc);
+    } else {
+        const uint64_t n_units = uint64_t(E) * n_tiles * n_groups;
+        const dim3 grid(uint32_t((n_units + kRowsWaves - 1) / kRowsWaves));
+        hipLaunchKernelGGL(k_vote_rows<R>, grid, dim3(kRowsThreads), 0, s, c->d_dir_tab, c->d_row_off, c->d_row_ok,
+                           c->spec.n_layers, c->rows, c->spec.n_phi, c->shift, n_tiles, n_groups, n_units, acc);
+    }
 }
 
 }  // namespace
@@ -171,8 +244,16 @@ bool rows_vote_default(const hough_ctx *c, uint32_t n_events)
 hipError_t launch_vote_rows(hough_ctx *c, const hough_hits *h, uint16_t *acc, hipStream_t s)
 {
     const uint32_t E = h->n_events;
-    hipError_t err = launch_vote_bounds(c, h, s);
-    if (err != hipSuccess) return err;
+    // one launch where finding the table again in every workgroup is cheap
+    // (both ways in us: 256 x 256 cells 2000 hits 8.9 / 10.6, 8000 hits 9.8 /
+    // 10.8, 16,000 11.5 / 10.5; 512 x 512 cells 6000 hits 11.2 / 11.1; 30
+    // events of 256 x 256 and 2000 hits 13.9 / 15.3)
+    const bool own = uint64_t(c->spec.n_layers) * c->spec.n_phi <= kRowsOwnEntries &&
+                     h->n_hits <= uint64_t(kRowsOwnHits) * E;
+    if (!own) {
+        const hipError_t err = launch_vote_bounds(c, h, s);
+        if (err != hipSuccess) return err;
+    }
     // rows per wave: eight share the loads best, but sixteen waves per compute
     // unit come first (16 events of 512 x 512: 17.1 us at four rows, 19.6 at
     // eight); two rows need no more entries than one (1024 x 1024: 9.8 us at
@@ -183,9 +264,9 @@ hipError_t launch_vote_rows(hough_ctx *c, const hough_hits *h, uint16_t *acc, hi
     KernelTimer t;
     prof_begin(c, "vote_rows", s, &t);
     switch (R) {
-    case 2: launch_rows_r<2>(c, E, acc, s); break;
-    case 4: launch_rows_r<4>(c, E, acc, s); break;
-    default: launch_rows_r<8>(c, E, acc, s); break;
+    case 2: launch_rows_r<2>(c, h, own, acc, s); break;
+    case 4: launch_rows_r<4>(c, h, own, acc, s); break;
+    default: launch_rows_r<8>(c, h, own, acc, s); break;
     }
     prof_end(c, s, &t);
     return hipGetLastError();
