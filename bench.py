@@ -52,6 +52,8 @@ VOTE_KERNEL_BYTES = {
     "vote_lds": lambda n_hits, cells: 5 * n_hits + 2 * cells,
     "vote_bounds": lambda n_hits, cells: 5 * n_hits,
     "vote_direct": lambda n_hits, cells: 2 * cells,
+    "vote_rows": lambda n_hits, cells: 2 * cells,
+    "vote_rows_own": lambda n_hits, cells: 5 * n_hits + 2 * cells,
     "vote_scan": lambda n_hits, cells: 5 * n_hits,
     "vote_gaps": lambda n_hits, cells: 2 * cells,
     # rank form: whole events per workgroup read their hits and write their
@@ -294,14 +296,15 @@ def bench_batched(H, torch, reps=5):
         stream.synchronize()
         ctx.set_profiling(False)
         times = ctx.kernel_times()
-    vk = next(k for k in ("vote_rank_event", "vote_rank_tile", "vote_direct", "vote_gaps", "vote_lds") if k in times)
+    vk = next(k for k in ("vote_rank_event", "vote_rank_tile", "vote_rows", "vote_rows_own", "vote_direct", "vote_gaps",
+                          "vote_lds") if k in times)
     t_vote = kernel_avg_ms(times, vk) * 1e-3
     vote_bytes = VOTE_KERNEL_BYTES[vk](batch.n_hits, E * ctx.cells)
     gbs = vote_bytes / t_vote / 1e9
     stage_bytes = 5 * batch.n_hits + 2 * E * ctx.cells
     t_stage = sum(kernel_avg_ms(times, k) for k in ("vote_bounds", "vote_direct", "vote_scan", "vote_gaps",
                                                      "vote_lds", "bucket_layers", "vote_rank_event",
-                                                     "vote_rank_tile")
+                                                     "vote_rank_tile", "vote_rows", "vote_rows_own")
                   if k in times) * 1e-3
 
     # the per-hit LDS-atomic form of the vote (the paper's recipe), timed once
@@ -391,7 +394,7 @@ TRAFFIC_KERNELS = {
     # bench name: (rocprofv3 kernel-name prefix, source file, workload); the
     # probe's largest dispatch of a prefix is the named workload's
     "rz_vote": ("hough::k_rz_vote_fast", "paper_1310_7556_amd/csrc/k_rz.hip", "c2_single_1ktrk_rz"),
-    "vote_direct": ("hough::k_vote_direct", "paper_1310_7556_amd/csrc/k_vote_direct.hip", "c2_single_1ktrk_rz"),
+    "vote_rows": ("hough::k_vote_rows<", "paper_1310_7556_amd/csrc/k_vote_rows.hip", "c2_single_1ktrk_rz"),
     "vote_rank_tile": ("hough::k_vote_rank<2, 10, true, false>", "paper_1310_7556_amd/csrc/k_vote_rank.hip",
                        "c4_batch_4096"),
     "vote_rank_event": ("hough::k_vote_rank<2, 10, true, true>", "paper_1310_7556_amd/csrc/k_vote_rank.hip",
@@ -559,11 +562,12 @@ def recorded_traffic(name):
 
 
 # Lane operations per (cell, layer) decision of the vote forms that decide
-# every cell: the direct form uses three VALU instructions per 64 decisions
+# every cell: the direct and row forms use three VALU instructions per 64 decisions
 # (subtract, subtract with borrow, add with carry); the rank form five per
 # 4 x 64 (two subtracts, a three-input bit operation, a shift and a bit-field
 # insert on four byte lanes).  Their ALU roof, beside the HBM one.
-VOTE_LANE_OPS_PER_DECISION = {"vote_direct": 3.0, "vote_rank_event": 1.25, "vote_rank_tile": 1.25}
+VOTE_LANE_OPS_PER_DECISION = {"vote_direct": 3.0, "vote_rows": 3.0, "vote_rows_own": 3.0,
+                              "vote_rank_event": 1.25, "vote_rank_tile": 1.25}
 
 
 def vote_alu_view(kernel, cells, layers, seconds):

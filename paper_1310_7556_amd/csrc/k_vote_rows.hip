@@ -262,7 +262,7 @@ hipError_t launch_vote_rows(hough_ctx *c, const hough_hits *h, uint16_t *acc, hi
     uint32_t R = 8;
     while (R > 2 && waves / R < 16 * uint64_t(c->n_cu)) R >>= 1;
     KernelTimer t;
-    prof_begin(c, "vote_rows", s, &t);
+    prof_begin(c, own ? "vote_rows_own" : "vote_rows", s, &t);
     switch (R) {
     case 2: launch_rows_r<2>(c, h, own, acc, s); break;
     case 4: launch_rows_r<4>(c, h, own, acc, s); break;
