@@ -168,8 +168,10 @@ typedef struct {
     uint32_t vote_wgs_per_cu;       /* persistent vote grid: workgroups per compute unit */
     uint32_t peak_rows;             /* accumulator rows per peak-finding tile (per wavefront strip in
                                        peak form 2) */
-    uint32_t rz_waves_per_cu;       /* persistent rz grid: waves per compute unit */
-    uint32_t vote_algo;             /* 0 = default (5 where usable, else 4), 1 = per-hit LDS atomics,
+    uint32_t rz_waves_per_cu;       /* persistent rz grid: waves per compute unit (any rz knob set keeps the
+                                       one-wave form also where cells hold many members) */
+    uint32_t vote_algo;             /* 0 = default (rows of few events in one pass up to 2^22 cells when
+                                       no vote knob is set, else 5 where usable, else 4), 1 = per-hit LDS atomics,
                                        2 = global atomics, 3 = hit-gap lists, 4 = bucket bounds (direct
                                        occupancy), 5 = bucket bounds in tile rank space, four cells per
                                        operation (n_phi 256, 512 or 1024; accumulator 8-byte aligned,
@@ -180,8 +182,9 @@ typedef struct {
                                        bounds found in LDS; grids of at most 1024 rows whose tables fit in
                                        LDS, else as 2), 2 = one row tile per workgroup (bounds from a table
                                        pass over the hits) */
-    uint32_t peak_algo;             /* peak search: 0 = default (2 where usable, else 1), 1 = tiles staged
-                                       in LDS, 2 = row window in registers (n_phi 256, 512 or 1024,
+    uint32_t peak_algo;             /* peak search: 0 = default (one launch, rows in registers, where peak_rows
+                                       is 0 too and n_phi is 256 to 2048; else 2 where usable, else 1),
+                                       1 = tiles staged in LDS, 2 = row window in registers (n_phi 256, 512 or 1024,
                                        accumulator 16-byte aligned, 8 for n_phi 256) */
     uint32_t rz_member_cap;         /* rz: members a candidate may have on the fast path (a power of two,
                                        256 to 4096; more go to the exact path); 0 = 112 with 4-bit
@@ -239,7 +242,7 @@ int hough_peaks(hough_ctx *ctx, const uint16_t *acc, uint32_t n_events,
 
 /* hough_peaks for callers that cannot allocate device memory (code under
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc):
- * the same results from the same kernels, but the peak search's scratch
+ * the same results from the two-pass kernels, whose scratch
  * (per-tile peak counts, their prefix and the scan's block sums) lives in
  * one static device array of 8 MiB per GPU, held until the process ends,
  * instead of the context's buffers.  The call itself allocates nothing

@@ -1,6 +1,7 @@
 // Step 1 of the transform in its direct bin-occupancy form (Section 4, first
-// step; the Discussion's A[B[i]] += 1 in layer-mask form), the default vote
-// algorithm.
+// step; the Discussion's A[B[i]] += 1 in layer-mask form), chosen where
+// neither the row form nor the rank form applies (k_vote_rows.hip,
+// k_vote_rank.hip); the bounds kernels serve all three.
 //
 // Split a row's offset as o = J W + f (J = o >> s, f = o mod W, W = 2^s) and
 // the azimuth circle into W-wide buckets aligned at 0.  Bin p of the row is

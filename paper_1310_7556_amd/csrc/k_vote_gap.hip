@@ -1,5 +1,5 @@
 // Step 1 of the transform in its exact gap form (Section 4, first step; the
-// Discussion's A[B[i]] += 1 in layer-mask form), the default vote algorithm.
+// Discussion's A[B[i]] += 1 in layer-mask form).
 //
 // A cell (row r, bin p) gets layer bit l iff some hit of layer l lies in the
 // bin's azimuth interval [O[l][r] + p W, O[l][r] + (p+1) W), W = 2^32/n_phi.

@@ -1,6 +1,7 @@
 // Step 1 of the transform (Section 4, first step; the Discussion's
 // A[B[i]] += 1 in its layer-mask form) in a rank form that decides four
-// (cell, layer) pairs with one 32-bit operation.  The default vote.
+// (cell, layer) pairs with one 32-bit operation.  The default vote
+// beyond the sizes of the row form (k_vote_rows.hip).
 //
 // Bin p of row r (offset o = J W + F, W = 2^32 / n_phi) holds a hit of layer
 // l unless bucket j = J + p is empty at F: F in [lo_j, hi_j], with lo_j the
@@ -25,8 +26,8 @@
 // Items are (event, run of 128-row tiles).  With BOUNDS an item covers a
 // whole event and first finds the bucket bounds from the event's hits in
 // LDS (the hits are read once, no table goes through HBM); otherwise the
-// bounds come from k_vote_bounds' per-event table, for single large events
-// split into many items.
+// bounds come from the per-event table (launch_vote_bounds), for batches of
+// fewer events split into many items.
 #include <algorithm>
 #include <vector>
 

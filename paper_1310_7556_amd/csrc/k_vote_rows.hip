@@ -18,6 +18,8 @@
 // where a launch that does nothing takes 4.5 (rank form, tile by tile: 32 and
 // 18; direct form: 12 and 10).  Four layers' entries at a time: all ten of a
 // ten-layer grid take the same 7 to 10 us with 150 registers for 82.
+#include <algorithm>
+
 #include "device_hits.h"
 #include "hough_internal.h"
 
@@ -27,8 +29,9 @@ namespace {
 
 constexpr uint32_t kRowsThreads = 256, kRowsWaves = kRowsThreads / 64;
 // What a workgroup that finds the table itself takes: (layer, bucket) entries
-// (20 KB of LDS) and mean hits per event.
-constexpr uint32_t kRowsOwnEntries = 2560, kRowsOwnHits = 8192;
+// (20 KB of LDS), mean hits per event, and hits in all (one event may hold
+// them all, and every workgroup walks its whole event).
+constexpr uint32_t kRowsOwnEntries = 2560, kRowsOwnHits = 8192, kRowsOwnHitsAll = 32768;
 
 // m[k] = 2 m[k] + [(f - e[k].lo) mod 2^32 > e[k].span] for four cells, f
 // wave-uniform: a subtract, a subtract whose borrow is the comparison, an add
@@ -246,10 +249,10 @@ hipError_t launch_vote_rows(hough_ctx *c, const hough_hits *h, uint16_t *acc, hi
     const uint32_t E = h->n_events;
     // one launch where finding the table again in every workgroup is cheap
     // (both ways in us: 256 x 256 cells 2000 hits 8.9 / 10.6, 8000 hits 9.8 /
-    // 10.8, 16,000 11.5 / 10.5; 512 x 512 cells 6000 hits 11.2 / 11.1; 30
-    // events of 256 x 256 and 2000 hits 13.9 / 15.3)
+    // 10.8, 16,000 11.5 / 10.5; 512 x 512 cells 6000 hits 11.2 / 11.1; 16
+    // events of 256 x 256 and 2000 hits 10.6 / 11.5)
     const bool own = uint64_t(c->spec.n_layers) * c->spec.n_phi <= kRowsOwnEntries &&
-                     h->n_hits <= uint64_t(kRowsOwnHits) * E;
+                     h->n_hits <= std::min(uint64_t(kRowsOwnHits) * E, uint64_t(kRowsOwnHitsAll));
     if (!own) {
         const hipError_t err = launch_vote_bounds(c, h, s);
         if (err != hipSuccess) return err;

@@ -39,6 +39,7 @@ def layers(n):
     ([8192], dict(n_phi=256, n_qpt=37), 0),                     # the most hits a workgroup walks for its own table
     ([8193], dict(n_phi=256, n_qpt=37), 1),
     ([16300, 9, 0], dict(n_phi=128, n_qpt=33), 3),              # their mean is what counts
+    ([8000, 8000, 8000, 8000, 769], dict(n_phi=64, n_qpt=9), 0),   # one hit too many in all
     ([600], dict(n_phi=256, n_qpt=37, **layers(11)), 0),        # more entries than a workgroup finds itself
     ([270000], dict(n_phi=256, n_qpt=37), 0),                   # a very large event: bounds in 64 parts
     ([20000, 0, 3], dict(n_phi=64, n_qpt=5), 1),                # no vector loads, one part each: by layer
