@@ -285,29 +285,53 @@ k_sector_count(const uint8_t *__restrict__ layer, const uint32_t *__restrict__ p
 }
 
 // part_cnt[k][bin] becomes the part's first position in the bin, relative to
-// the event; bin_off[e][0 .. kSectorBins]: the bins' starts.
-__global__ void __launch_bounds__(kSectorBins)
+// the event; bin_off[e][0 .. kSectorBins]: the bins' starts.  Bound by the
+// walk over the event's parts, so four threads share a bin, each a quarter of
+// them, sixteen loads together (one event of 60,000 hits, 58 parts, 7.4 -> 3.8
+// us; 16 events of 100 to 10,000 tracks 9.0 -> 6.7; one event of 600,000 hits,
+// the whole index 54 -> 49).
+constexpr uint32_t kPlanShares = 4, kPlanThreads = kPlanShares * kSectorBins, kPlanBatch = 16;
+
+__global__ void __launch_bounds__(kPlanThreads)
 k_sector_plan(uint32_t K, uint32_t *__restrict__ part_cnt, uint32_t *__restrict__ bin_off)
 {
-    __shared__ uint32_t tot[kSectorBins];
-    __shared__ uint32_t wsum[kSectorBins / 64];
-    const uint32_t t = threadIdx.x;
-    uint32_t *pc = part_cnt + size_t(blockIdx.x) * K * kSectorBins + t;
-    uint32_t s = 0;
-#pragma unroll 16
-    for (uint32_t k = 0; k < K; ++k) s += pc[k * kSectorBins];
-    tot[t] = s;
+    __shared__ uint32_t share_s[kPlanShares][kSectorBins], tot[kSectorBins];
+    __shared__ uint32_t wsum[kPlanThreads / 64];
+    const uint32_t bin = threadIdx.x % kSectorBins, share = threadIdx.x / kSectorBins;
+    const uint32_t k0 = K * share / kPlanShares, k1 = K * (share + 1) / kPlanShares;
+    uint32_t *pc = part_cnt + size_t(blockIdx.x) * K * kSectorBins + bin;
+    auto batch = [&](uint32_t k, uint32_t (&x)[kPlanBatch]) {
+#pragma unroll
+        for (uint32_t u = 0; u < kPlanBatch; ++u) x[u] = pc[size_t(min(k + u, k1 - 1)) * kSectorBins];
+    };
+    uint32_t s = 0, x[kPlanBatch];
+    for (uint32_t k = k0; k < k1; k += kPlanBatch) {
+        batch(k, x);
+#pragma unroll
+        for (uint32_t u = 0; u < kPlanBatch; ++u) s += k + u < k1 ? x[u] : 0u;
+    }
+    share_s[share][bin] = s;
     __syncthreads();
-    const uint32_t all = block_prefix<kSectorBins>(tot, kSectorBins, wsum);
-    uint32_t run = tot[t];
+    uint32_t all = 0, run = 0;
+#pragma unroll
+    for (uint32_t i = 0; i < kPlanShares; ++i) {
+        run += i < share ? share_s[i][bin] : 0u;
+        all += share_s[i][bin];
+    }
+    if (share == 0) tot[bin] = all;
+    __syncthreads();
+    all = block_prefix<kPlanThreads>(tot, kSectorBins, wsum);
+    run += tot[bin];
     uint32_t *bo = bin_off + size_t(blockIdx.x) * (kSectorBins + 1);
-    bo[t] = run;
-    if (t == 0) bo[kSectorBins] = all;
-#pragma unroll 16
-    for (uint32_t k = 0; k < K; ++k) {
-        const uint32_t x = pc[k * kSectorBins];
-        pc[k * kSectorBins] = run;
-        run += x;
+    if (share == 0) bo[bin] = run;
+    if (threadIdx.x == 0) bo[kSectorBins] = all;
+    for (uint32_t k = k0; k < k1; k += kPlanBatch) {
+        if (k1 - k0 > kPlanBatch) batch(k, x);       // else still there
+#pragma unroll
+        for (uint32_t u = 0; u < kPlanBatch; ++u) {
+            if (k + u < k1) pc[size_t(k + u) * kSectorBins] = run;
+            run += x[u];
+        }
     }
 }
 
@@ -508,7 +532,7 @@ void launch_index(hough_ctx *c, const hough_hits *h, hipStream_t s)
     const uint32_t K = index_parts(c, E, h->n_hits), sbits = std::min(kSectorBits, bits);
     hipLaunchKernelGGL(k_sector_count, dim3(E * K), dim3(kSplitThreads), 0, s, h->layer, h->phi, h->event_offsets,
                        h->n_hits, L, sbits, K, vec, c->d_sec_part);
-    hipLaunchKernelGGL(k_sector_plan, dim3(E), dim3(kSectorBins), 0, s, K, c->d_sec_part, c->d_sec_off);
+    hipLaunchKernelGGL(k_sector_plan, dim3(E), dim3(kPlanThreads), 0, s, K, c->d_sec_part, c->d_sec_off);
     hipLaunchKernelGGL(k_sector_scatter<Z>, dim3(E * K), dim3(kSplitThreads), 0, s, h->layer, h->phi, h->z_um,
                        h->event_offsets, h->n_hits, L, sbits, K, c->d_sec_part, mid);
     hipLaunchKernelGGL(k_sector_sort<Z>, dim3(E * (L << sbits)), dim3(kSplitThreads), 0, s, mid, h->event_offsets,

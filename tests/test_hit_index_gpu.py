@@ -48,6 +48,8 @@ def run(H, spec, batch, shift=0):
     ([3001, 403], dict(n_phi=128, n_qpt=3), dict(shift=1)),        # unaligned arrays, whole form
     ([50000], dict(n_phi=512, n_qpt=1), dict(layers=200)),         # hits of layers the detector lacks
     ([4000, 300], dict(n_phi=64, n_qpt=4), dict(layers=200)),
+    ([480] * 1100, dict(n_phi=64, n_qpt=1, n_cot=3), {}),          # split form, one part per event
+    ([300_000, 11], dict(n_phi=512, n_qpt=1, n_cot=3), {}),        # 146 parts per event
 ])
 def test_rz_over_the_hit_index(H, sizes, kw, opts):  # noqa: F811
     spec = small_spec(**dict(dict(n_cot=20), **kw))
