@@ -76,13 +76,15 @@ struct RzParams {
     uint32_t mcap;                // fast path: member list capacity
 };
 
-// How the fast kernel hands out candidates.  A list of up to kRzShareMax per
-// wave is divided evenly, a contiguous share for each wave, an XCD's shares
-// side by side: tickets of kRzChunk leave waves idle or with twice the work
-// of others (12 members per cell, 4096 waves: 1024 candidates 95 us by
-// tickets, 23 by shares, 16,384 130 and 54, 43,203 137 and 95, 59,512 190 and
-// 127; 92,778 of 18 249 and 210, 161,779 of 29 459 and 450; 398,477 of 20 865
-// and 909, where the longest share decides).
+// How the fast kernel hands out candidates.  In a list of up to kRzShareMax
+// per wave every wave takes each gridDim-th one, the waves of an XCD side by
+// side: tickets of kRzChunk leave waves idle or with twice the work of others
+// (12 members per cell, 4096 waves: 1024 candidates 95 us by tickets, 23 so;
+// 16,384 113 and 53, 43,203 144 and 95, 59,512 170 and 127; 92,778 of 18 246
+// and 212, 120,174 of 47 469 and 467; 182,486 of 44 628 and 644, 240,289 of 47
+// 823 and 880, where the fullest wave decides).  Contiguous shares are the
+// slower where events differ: 8 of 10 to 1000 tracks, 252,541 candidates, 704
+// us, each gridDim-th 649.
 // Longer lists are split into kRzQueues contiguous ranges, one per XCD, each
 // with its own counter (kRzQueueStride dwords apart, in different cache
 // lines); a wave starts on the queue of the XCD it runs on (read from the
@@ -93,7 +95,7 @@ struct RzParams {
 // to the next queue.  (1000-track event: 0.96 ms with 8 queues of 8-candidate
 // tickets; 1.00 ms with one queue, 0.99 and 0.98 ms with tickets of 4 and 16,
 // 1.04 and 1.17 ms with 32 and 64 queues.)
-constexpr uint32_t kRzShareMax = 64;
+constexpr uint32_t kRzShareMax = 32;
 constexpr uint32_t kRzQueues = 8;
 constexpr uint32_t kRzQueueStride = 32;
 constexpr uint32_t kRzChunk = 8;
@@ -466,13 +468,14 @@ k_rz_vote_fast(RzParams P)
       const uint64_t qb = total * q / kRzQueues, qe = total * (q + 1) / kRzQueues;
       uint32_t *qc = P.counter + q * kRzQueueStride;
       for (uint32_t round = 0;; ++round) {
-        uint64_t c0, c1;
+        uint64_t c0, c1, cs = 1;
         if (shares) {
             if (round) break;
             const uint32_t g = gridDim.x, b = blockIdx.x, w = g % kRzQueues ? b : b % kRzQueues * (g / kRzQueues) + b / kRzQueues;
-            c0 = total * w / g;
-            c1 = total * (w + 1) / g;
-            if (c0 == c1) break;
+            c0 = w;
+            c1 = total;
+            cs = g;
+            if (c0 >= c1) break;
         } else {
             c0 = qb + uni(atomicAdd(qc, lane == 0 ? kRzChunk : 0u));
             if (c0 >= qe) break;
@@ -481,9 +484,9 @@ k_rz_vote_fast(RzParams P)
         // the next candidate's peak record is fetched while the current one
         // is processed, so its latency overlaps the current loads
         uint2 nrec = rz_record(P, c0);
-      for (uint64_t c = c0; c < c1; ++c) {
+      for (uint64_t c = c0; c < c1; c += cs) {
         const uint2 rec = nrec;
-        if (c + 1 < c1) nrec = rz_record(P, c + 1);
+        if (c + cs < c1) nrec = rz_record(P, c + cs);
         const RzCand r = rz_decode_rec(P, c, rec);
         const uint32_t k = r.k, p = r.p;
         // all layers' (Z + z0_lo) for this lane's first cot bin, issued now
